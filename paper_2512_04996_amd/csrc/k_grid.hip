@@ -503,7 +503,8 @@ __device__ __forceinline__ void rank_sort_block(int bid, const float* __restrict
                                                         const BlockJob* __restrict__ jobs, const uint32_t* __restrict__ vox,
                                                         const uint32_t* __restrict__ hist, const uint32_t* __restrict__ off,
                                                         const uint32_t* __restrict__ tmp, uint32_t* __restrict__ vm,
-                                                        float4* __restrict__ qs4, uint32_t sort_min)
+                                                        float4* __restrict__ qs4, uint8_t* __restrict__ pyr,
+                                                        uint32_t sort_min)
 {
     __shared__ uint32_t chunk[kThreads / 64][kCoopChunk];
     const BlockJob job = jobs[bid];
@@ -523,6 +524,7 @@ __device__ __forceinline__ void rank_sort_block(int bid, const float* __restrict
     const uint32_t r = coop ? rank_in_wave(tmp, cs, c, e, chunk[threadIdx.x / 64]) : rank_in(tmp, cs, c, e);
     vm[(int64_t)og + 2 + r] = e;
     qs4[cs + r] = make_float4(qx[ge], qy[ge], qz[ge], __uint_as_float(e));
+    if (r == 0) mark_occupied(P, (uint32_t)(g - P.v_base), pyr);   // one point of each occupied voxel
 }
 
 __global__ __launch_bounds__(kThreads) void k_rank_sort(const float* __restrict__ qx, const float* __restrict__ qy,
@@ -530,9 +532,10 @@ __global__ __launch_bounds__(kThreads) void k_rank_sort(const float* __restrict_
                                                         const BlockJob* __restrict__ jobs, const uint32_t* __restrict__ vox,
                                                         const uint32_t* __restrict__ hist, const uint32_t* __restrict__ off,
                                                         const uint32_t* __restrict__ tmp, uint32_t* __restrict__ vm,
-                                                        float4* __restrict__ qs4, uint32_t sort_min)
+                                                        float4* __restrict__ qs4, uint8_t* __restrict__ pyr,
+                                                        uint32_t sort_min)
 {
-    rank_sort_block((int)blockIdx.x, qx, qy, qz, pd, jobs, vox, hist, off, tmp, vm, qs4, sort_min);
+    rank_sort_block((int)blockIdx.x, qx, qy, qz, pd, jobs, vox, hist, off, tmp, vm, qs4, pyr, sort_min);
 }
 
 // Long segments (kSegSortMin to kSegSortMax points) of a single-pair grid,
@@ -564,7 +567,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_segments(
     const float* __restrict__ qx, const float* __restrict__ qy, const float* __restrict__ qz,
     const PairDev* __restrict__ pd, const uint32_t* __restrict__ big_list, const uint32_t* __restrict__ big_count,
     const uint32_t* __restrict__ hist, const uint32_t* __restrict__ off, const uint32_t* __restrict__ tmp,
-    uint32_t* __restrict__ vm, float4* __restrict__ qs4)
+    uint32_t* __restrict__ vm, float4* __restrict__ qs4, uint8_t* __restrict__ pyr)
 {
     constexpr int kW = kSortThreads / 64;
     constexpr uint32_t kPer = kBitmapWords / kSortThreads;   // bitmap words per thread
@@ -578,6 +581,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_segments(
         const uint32_t g = big_list[b];
         const uint32_t c = hist[g];
         if (c > kSegSortMax) continue;   // uniform over the block: ranked point by point
+        if (threadIdx.x == 0) mark_occupied(P, g - (uint32_t)P.v_base, pyr);
         const uint32_t og = off[g];
         const int64_t cs = (int64_t)og - 2 * (int64_t)g;
         // the range of the segment's indices
@@ -915,14 +919,14 @@ __global__ __launch_bounds__(kThreads) void k_rank_pair(
     const float* __restrict__ qx, const float* __restrict__ qy, const float* __restrict__ qz,
     const PairDev* __restrict__ pd, const BlockJob* __restrict__ qjobs, int nq, const uint32_t* __restrict__ vox,
     const uint32_t* __restrict__ hist, const uint32_t* __restrict__ off, const uint32_t* __restrict__ tmp,
-    uint32_t* __restrict__ vm, float4* __restrict__ qs4, const BlockJob* __restrict__ pjobs,
-    const float* __restrict__ px, const float* __restrict__ py, const float* __restrict__ pz,
+    uint32_t* __restrict__ vm, float4* __restrict__ qs4, uint8_t* __restrict__ pyr,
+    const BlockJob* __restrict__ pjobs, const float* __restrict__ px, const float* __restrict__ py, const float* __restrict__ pz,
     const uint32_t* __restrict__ skey, const uint32_t* __restrict__ soff, const uint32_t* __restrict__ sidx,
     const int32_t* __restrict__ sbig, float4* __restrict__ ps4)
 {
     const int b = (int)blockIdx.x;
     if (b < nq)
-        rank_sort_block(b, qx, qy, qz, pd, qjobs, vox, hist, off, tmp, vm, qs4, 0xFFFFFFFFu);
+        rank_sort_block(b, qx, qy, qz, pd, qjobs, vox, hist, off, tmp, vm, qs4, pyr, 0xFFFFFFFFu);
     else
         src_rank_block(b - nq, pd, pjobs, px, py, pz, skey, soff, sidx, sbig, ps4);
 }
@@ -995,19 +999,20 @@ void launch_place(const PairDev* pd, const BlockJob* jobs, int njobs, const uint
 
 void launch_rank_sort(const float* qx, const float* qy, const float* qz, const PairDev* pd, const BlockJob* jobs,
                       int njobs, const uint32_t* vox, const uint32_t* hist, const uint32_t* off, const uint32_t* tmp,
-                      uint32_t* vm, float4* qs4, hipStream_t s, uint32_t sort_min)
+                      uint32_t* vm, float4* qs4, uint8_t* pyr, hipStream_t s, uint32_t sort_min)
 {
     if (njobs <= 0) return;
     launch_timed(k_rank_sort, dim3(njobs), dim3(kThreads), s, qx, qy, qz, pd, jobs, vox, hist, off, tmp, vm, qs4,
-                 sort_min);
+                 pyr, sort_min);
 }
 
 void launch_sort_segments(const float* qx, const float* qy, const float* qz, const PairDev* pd,
                           const uint32_t* big_list, const uint32_t* big_count, const uint32_t* hist,
-                          const uint32_t* off, const uint32_t* tmp, uint32_t* vm, float4* qs4, hipStream_t s)
+                          const uint32_t* off, const uint32_t* tmp, uint32_t* vm, float4* qs4, uint8_t* pyr,
+                          hipStream_t s)
 {
     launch_timed(k_sort_segments, dim3(kSortBlocks), dim3(kSortThreads), s, qx, qy, qz, pd, big_list, big_count, hist, off,
-                 tmp, vm, qs4);
+                 tmp, vm, qs4, pyr);
 }
 
 void launch_clear4(uint32_t* a, int64_t na, unsigned long long* b, int64_t nb, uint32_t* c, int64_t nc, uint32_t* d,
@@ -1090,13 +1095,13 @@ void launch_place_pair(const PairDev* pd, const BlockJob* qjobs, int nq, const u
 
 void launch_rank_pair(const float* qx, const float* qy, const float* qz, const PairDev* pd, const BlockJob* qjobs,
                       int nq, const uint32_t* vox, const uint32_t* hist, const uint32_t* off, const uint32_t* tmp,
-                      uint32_t* vm, float4* qs4, const BlockJob* pjobs, int np, const float* px, const float* py,
-                      const float* pz, const uint32_t* skey, const uint32_t* soff, const uint32_t* sidx,
-                      const int32_t* sbig, float4* ps4, hipStream_t s)
+                      uint32_t* vm, float4* qs4, uint8_t* pyr, const BlockJob* pjobs, int np, const float* px,
+                      const float* py, const float* pz, const uint32_t* skey, const uint32_t* soff,
+                      const uint32_t* sidx, const int32_t* sbig, float4* ps4, hipStream_t s)
 {
     if (nq + np <= 0) return;
     launch_timed(k_rank_pair, dim3(nq + np), dim3(kThreads), s, qx, qy, qz, pd, qjobs, nq, vox, hist, off, tmp, vm,
-                 qs4, pjobs, px, py, pz, skey, soff, sidx, sbig, ps4);
+                 qs4, pyr, pjobs, px, py, pz, skey, soff, sidx, sbig, ps4);
 }
 
 }  // namespace vicp

@@ -22,8 +22,10 @@
 // counts the smaller indices of its bucket), so the bucketed copy, and every
 // per-block sum taken over it, is the same from run to run.
 //
-// Global search (empty undilated voxel or outside the grid): the query is
-// appended to a per-pair list and an exact brute force over all targets
+// Global search (empty undilated voxel or outside the grid): the wave
+// resolves the query itself by an exact search of the occupancy pyramid.
+// Exhaustive search (the comparator, and queries without a finite distance):
+// the query is appended to a per-pair list and a brute force over all targets
 // resolves it; partial minima from target tiles merge through a 64-bit
 // atomic minimum of (distance bits << 32 | index), which is order-free, so
 // the result is deterministic.
@@ -93,178 +95,319 @@ __device__ __forceinline__ void consider(const float4& q, float sx, float sy, fl
     bz = better ? q.z : bz;
 }
 
-// Exact global search by voxel shells.  A query whose voxel is empty and
-// undilated, or outside the grid, takes the exact minimum of (d, j) over all
-// n targets (Alg. 4's global search).  Rather than scanning all n, the wave
-// visits the occupied voxels of a growing cube of voxels around the query's
-// voxel (clamped into the grid) and stops once every target outside the
-// visited cube is provably farther than the best found: its squared
-// distance is then above the best one even after the float32 rounding of
-// the distance, so it can neither win nor tie.  The bound takes each face of
-// the cube that is not on the grid's boundary: a target beyond it lies
-// beyond that face on its axis and inside the grid box on the other two.
-// Faces and the grid box are widened by a margin for the float32 rounding
+// Exact global search on the occupancy pyramid.  A query whose voxel is empty
+// and undilated, or outside the grid, takes the exact minimum of (d, j) over
+// all n targets (Alg. 4's global search).  One wave resolves one query: the
+// pyramid is a 64-ary tree (4 x 4 x 4 cells per cell above), so a lane holds
+// one child of the current node, its occupied flag and a lower bound on the
+// squared distance of any target in it; the wave takes the children nearest
+// first and drops every child whose bound is above the best distance found.
+// A query within reach of the surface first reads one cube of voxels around
+// its own (clamped into the grid), which settles most misses in two rounds of
+// loads.  The tree starts in the 16^3-voxel node around that voxel and climbs
+// only while a target outside the node could still win; a far query descends
+// from the top.  Level-1 cells (bricks of 64 voxels) are taken kN at a time.
+// Voxels are read as rows along x, whose points are consecutive: two offsets
+// give a whole row's.
+//
+// Cells, and the grid box, are widened by a margin for the float32 rounding
 // of the voxel assignment (floor((q - o) * inv)), so a target assigned to a
-// voxel may lie slightly outside it.  All 64 lanes call it with the same
-// point; every lane gets the result.  False (nothing found) when a cube of
-// kShellMax voxels around does not settle it: the query then goes to the
-// exhaustive search, and so does a query whose cube holds so many points
-// that a lane would scan more than kShellPoints of them (coarse grids with
-// thousands of points in a voxel: the tiled exhaustive search is the faster
-// there).  Each batch of a lane's voxels loads its directory entries
-// together, then the points of its occupied voxels as one flat run (so a
-// lane waits for two rounds of loads per batch, not one per voxel).
-constexpr int kShellFirst = 2;   // the smallest first cube: 5^3 voxels
-constexpr int kShellMax = 8;     // the largest: 17^3 voxels
-constexpr int kShellBatch = 6;     // directory loads in flight per lane (registration)
-constexpr int kShellLoads = 4;     // point loads in flight per lane (registration)
-constexpr int kShellBatchNN = 12;  // the same in the correspondence search
-constexpr int kShellLoadsNN = 8;
-constexpr int kShellFirstNN = 4;   // its smallest first cube, 9^3 voxels: one round of 12 x 64 entries
-constexpr uint32_t kShellPoints = 384;   // points a lane may scan before the wave gives up
+// voxel may lie slightly outside it; a bound must exceed the best distance
+// by a factor 1 / (1 - 1e-4), far above the rounding of the float32
+// distance, so a dropped target can neither win nor tie.  All 64 lanes call
+// it with the same point; every lane gets the result.  False when the query
+// is not finite or no finite distance was found: it then goes to the
+// exhaustive search.
+//
+// What bounds it: the latency of its dependent loads (flags, offsets,
+// points).  Voxel cubes growing around the query, its former form, read
+// 9^3 to 17^3 directory entries per miss and sent what lay farther than
+// eight voxels to the exhaustive search.  A registration of two scans that
+// overlap in part (140k / 120k points, 10 to 30% misses, 30 iterations):
+// 88.3 ms before, 28.7 ms; the loss on 16 x 40k pairs (3.5% misses): 473 and
+// 393 us; a 2k sphere with 2% misses, 20 iterations: 568 and 479 us.  Reading
+// directory entries voxel by voxel instead of offsets row by row: 52.9 ms on
+// the first, 466 and 578 us on the others.
+constexpr float kBoundSlack = 1.0f - 1e-4f;
+constexpr uint32_t kSerialPoints = 96;   // points a lane scans alone; above that the wave scans row by row
+constexpr int kN = 2;                    // rows per lane and round: of a cube, or of as many bricks
+constexpr int kLoads = 4;                // point loads in flight per lane
+constexpr int kCubeMin = 2;              // the first cube's smallest radius (registration): 5^3 voxels
+constexpr int kCubeMinNN = 4;            // in the correspondence search, whose misses lie farther: 9^3 voxels
+constexpr int kCubeMax = 4;
 
-// The point and every quantity derived from it are the same in all lanes
-// (scalar registers); a lane keeps only its best candidate's (d, j) and
-// segment slot, and the winner's coordinates are read once at the end.
-template <int kBatch, int kLoads, int kFirst>
-__device__ __forceinline__ bool shell_nearest(const PairDev& P, const uint2* __restrict__ dir,
-                                              const float4* __restrict__ qs4, float sx, float sy, float sz,
-                                              float& rd, uint32_t& rj, float& rx, float& ry, float& rz)
+struct TreeBox {
+    float s[3], o[3], mg[3], vox;
+    int D[3];
+};
+
+// Lower bound on the squared distance from the query to any target in the
+// cell (x, y, z) of level l.
+__device__ __forceinline__ float cell_bound(const TreeBox& b, int l, int x, int y, int z)
+{
+    const uint32_t c[3] = {(uint32_t)x, (uint32_t)y, (uint32_t)z};   // (c + 1) 4^l < 2^32: D + 4^l < 2^31 + 2^30
+    float lb = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float lo = b.o[a] + (float)(c[a] << (2 * l)) * b.vox - b.mg[a];
+        const float hi = b.o[a] + (float)min((c[a] + 1u) << (2 * l), (uint32_t)b.D[a]) * b.vox + b.mg[a];
+        const float g = b.s[a] < lo ? lo - b.s[a] : (b.s[a] > hi ? b.s[a] - hi : 0.0f);
+        lb += g * g;
+    }
+    return lb;
+}
+
+// A lower bound on the squared distance to the voxels [x0, x1) of row (y, z).
+__device__ __forceinline__ float row_bound(const TreeBox& b, int x0, int x1, int y, int z)
+{
+    const float l[3] = {(float)x0, (float)y, (float)z}, h[3] = {(float)x1, (float)y + 1.0f, (float)z + 1.0f};
+    float lb = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float lo = b.o[a] + l[a] * b.vox - b.mg[a], hi = b.o[a] + h[a] * b.vox + b.mg[a];
+        const float g = b.s[a] < lo ? lo - b.s[a] : (b.s[a] > hi ? b.s[a] - hi : 0.0f);
+        lb += g * g;
+    }
+    return lb;
+}
+
+template <int kFirst>
+__device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* __restrict__ off,
+                                             const uint8_t* __restrict__ pyr, const float4* __restrict__ qs4, float sx,
+                                             float sy, float sz, float& rd, uint32_t& rj, float& rx, float& ry,
+                                             float& rz)
 {
     if (!(isfinite(sx) && isfinite(sy) && isfinite(sz))) return false;   // left to the exhaustive search
     const int lane = threadIdx.x & (kWave - 1);
-    const float inv = P.inv, vox = 1.0f / P.inv;
-    const float s[3] = {sx, sy, sz};
-    const float o[3] = {P.ox, P.oy, P.oz};
-    const int D[3] = {P.Dx, P.Dy, P.Dz};
-    int c[3];
-    float mg[3], d2box[3];
+    const int lx = lane & 3, ly = (lane >> 2) & 3, lz = lane >> 4;
+    TreeBox b;
+    b.s[0] = sx, b.s[1] = sy, b.s[2] = sz;
+    b.o[0] = P.ox, b.o[1] = P.oy, b.o[2] = P.oz;
+    b.D[0] = P.Dx, b.D[1] = P.Dy, b.D[2] = P.Dz;
+    b.vox = 1.0f / P.inv;
+    int v0[3];
+    float d2box[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const float f = (s[a] - o[a]) * inv;
-        c[a] = f < 0.0f ? 0 : (f >= (float)(D[a] - 1) ? D[a] - 1 : (int)floorf(f));
-        c[a] = __builtin_amdgcn_readfirstlane(c[a]);
+        const float f = (b.s[a] - b.o[a]) * P.inv;
+        const int c = f < 0.0f ? 0 : (f >= (float)(b.D[a] - 1) ? b.D[a] - 1 : (int)floorf(f));
+        v0[a] = __builtin_amdgcn_readfirstlane(c);
         // 1e-5 of the coordinates' magnitude and 1e-3 of a voxel: far above
         // the float32 rounding of the assignment and of this arithmetic
-        mg[a] = 1e-5f * (fabsf(o[a]) + ((float)D[a] + 1.0f) * vox) + 1e-3f * vox;
-        const float lo = o[a] - mg[a], hi = o[a] + (float)D[a] * vox + mg[a];
-        const float g = s[a] < lo ? lo - s[a] : (s[a] > hi ? s[a] - hi : 0.0f);
+        b.mg[a] = 1e-5f * (fabsf(b.o[a]) + ((float)b.D[a] + 1.0f) * b.vox) + 1e-3f * b.vox;
+        const float lo = b.o[a] - b.mg[a], hi = b.o[a] + (float)b.D[a] * b.vox + b.mg[a];
+        const float g = b.s[a] < lo ? lo - b.s[a] : (b.s[a] > hi ? b.s[a] - hi : 0.0f);
         d2box[a] = g * g;
     }
-    float bd = INFINITY;
-    uint32_t bj = 0xFFFFFFFFu, bslot = 0u;
-    uint32_t scanned = 0u;
-    int done_r = -1;   // the cube of this radius has been visited
-    // the first cube reaches one voxel past the dilation: a global search's
-    // voxel has no occupied voxel within L1 distance L
-    int R = min(max(P.pad + 1, kFirst), kShellMax);
-    while (true) {
-        const int w = 2 * R + 1;
-        const int items = w * w * w;
-        for (int i0 = lane; i0 < items; i0 += kWave * kBatch) {
-            // the batch's directory entries, all in flight together
-            uint2 e[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                e[u] = make_uint2(0u, 0u);
-                const int it = i0 + u * kWave;
-                if (it >= items) continue;
-                const int dz = it / (w * w) - R, rem = it % (w * w);
-                const int dy = rem / w - R, dx = rem % w - R;
-                if (max(abs(dx), max(abs(dy), abs(dz))) <= done_r) continue;   // visited before
-                const int vx = c[0] + dx, vy = c[1] + dy, vz = c[2] + dz;
-                if (vx < 0 || vy < 0 || vz < 0 || vx >= D[0] || vy >= D[1] || vz >= D[2]) continue;
-                e[u] = dir[P.v_base + vx + (int64_t)D[0] * (vy + (int64_t)D[1] * vz)];
-            }
-            // the points of the batch's occupied voxels (own count, no mask:
-            // a dilated voxel's entry points at its root, visited as itself)
-            // as one flat run, kLoads loads in flight; a lane past its last
-            // point repeats it (a repeat never wins)
-            uint32_t end[kBatch];
-            uint32_t total = 0u;
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                total += (e[u].y & kMask) ? 0u : e[u].y;
-                end[u] = total;
-            }
-            scanned += total;
-            if (__ballot(scanned > kShellPoints)) return false;   // uniform: too many points
-            for (uint32_t t0 = 0; t0 < total; t0 += kLoads) {
-                float4 q[kLoads];
-                uint32_t sl[kLoads];
-#pragma unroll
-                for (int t = 0; t < kLoads; ++t) {
-                    const uint32_t f = min(t0 + (uint32_t)t, total - 1u);
-                    uint32_t slot = 0u, start = 0u;
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) {
-                        const bool here = f >= start && f < end[u];
-                        slot = here ? e[u].x + (f - start) : slot;
-                        start = end[u];
-                    }
-                    sl[t] = slot;
-                    q[t] = qs4[slot];
-                }
-#pragma unroll
-                for (int t = 0; t < kLoads; ++t) {
-                    const float d = dist2(sx, sy, sz, q[t].x, q[t].y, q[t].z);
-                    const uint32_t j = __float_as_uint(q[t].w);
-                    const bool better = d < bd || (d == bd && j < bj);
-                    bd = better ? d : bd;
-                    bj = better ? j : bj;
-                    bslot = better ? sl[t] : bslot;
-                }
-            }
-        }
-        // the wave's minimum of (d, j): distances are >= 0, so their bits
-        // order as the values do
-        unsigned long long key = ((unsigned long long)__float_as_uint(bd) << 32) | bj;
-#pragma unroll
-        for (int m = 1; m < kWave; m <<= 1) {
-            const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(key >> 32), m, kWave);
-            const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)key, m, kWave);
-            const unsigned long long other = ((unsigned long long)hi << 32) | lo;
-            key = other < key ? other : key;
-        }
-        const float best = __uint_as_float((uint32_t)(key >> 32));
-        // lower bound on the squared distance of any target outside the
-        // visited cube
-        float lb2 = INFINITY;
-        bool all = true;
+    // a lower bound on the squared distance of any target outside the voxels
+    // [lo, hi): each of their faces that is not on the grid's boundary bounds
+    // those beyond it on its axis, the grid box on the other two
+    auto outside = [&](const int lo[3], const int hi[3]) {
+        float out = INFINITY;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const float rest = d2box[(a + 1) % 3] + d2box[(a + 2) % 3];
-            if (c[a] - R > 0) {   // targets below the cube's low face on axis a
-                all = false;
-                const float g = s[a] - (o[a] + (float)(c[a] - R) * vox + mg[a]);
-                lb2 = fminf(lb2, (g > 0.0f ? g * g : 0.0f) + rest);
+            if (lo[a] > 0) {
+                const float g = b.s[a] - (b.o[a] + (float)lo[a] * b.vox + b.mg[a]);
+                out = fminf(out, (g > 0.0f ? g * g : 0.0f) + rest);
             }
-            if (c[a] + R < D[a] - 1) {   // above its high face
-                all = false;
-                const float g = (o[a] + (float)(c[a] + R + 1) * vox - mg[a]) - s[a];
-                lb2 = fminf(lb2, (g > 0.0f ? g * g : 0.0f) + rest);
+            if (hi[a] < b.D[a]) {
+                const float g = (b.o[a] + (float)hi[a] * b.vox - b.mg[a]) - b.s[a];
+                out = fminf(out, (g > 0.0f ? g * g : 0.0f) + rest);
             }
         }
-        const bool found = (uint32_t)(key >> 32) != 0x7F800000u;   // a finite best
-        if (found && (all || lb2 * (1.0f - 1e-4f) > best)) {
-            const unsigned long long mine = ((unsigned long long)__float_as_uint(bd) << 32) | bj;
-            const int owner = __ffsll((long long)__ballot(mine == key)) - 1;
-            const float4 wq = qs4[__builtin_amdgcn_readlane((int)bslot, owner)];
-            rd = best;
-            rj = (uint32_t)key;
-            rx = wq.x;
-            ry = wq.y;
-            rz = wq.z;
-            return true;
+        return out;
+    };
+    // each lane keeps its own best; `best` is the wave's
+    float bd = INFINITY, bx = 0.0f, by = 0.0f, bz = 0.0f, best = INFINITY;
+    uint32_t bj = 0xFFFFFFFFu;
+    auto take = [&](const float4& q) {
+        const float d = dist2(sx, sy, sz, q.x, q.y, q.z);
+        const uint32_t j = __float_as_uint(q.w);
+        const bool better = d < bd || (d == bd && j < bj);
+        bd = better ? d : bd;
+        bj = better ? j : bj;
+        bx = better ? q.x : bx;
+        by = better ? q.y : by;
+        bz = better ? q.z : bz;
+    };
+    // the first cube reaches one voxel past the dilation: a global search's
+    // voxel has no occupied voxel within L1 distance L
+    const int top = P.t_top;
+    const int R = min(max(P.pad + 1, kFirst), kCubeMax);
+    const int w = 2 * R + 1;
+    static_assert((2 * kCubeMax + 1) * (2 * kCubeMax + 1) <= kN * kWave, "a cube's rows fit one round");
+    const float reach = (float)R * b.vox;
+    bool cube = top > 0 && d2box[0] + d2box[1] + d2box[2] <= reach * reach;
+    // the points of the voxels [x0, x1) of row (y, z): consecutive voxels'
+    // segments follow each other, and every voxel before g has two header
+    // words in off[g]
+    auto run = [&](int x0, int x1, int y, int z) {
+        const int64_t g0 = P.v_base + x0 + (int64_t)b.D[0] * (y + (int64_t)b.D[1] * z), g1 = g0 + (x1 - x0);
+        const uint32_t a0 = off[g0], a1 = off[g1];
+        return make_uint2(a0 - 2u * (uint32_t)g0, a1 - a0 - 2u * (uint32_t)(x1 - x0));
+    };
+    const int ry_ = (lane >> 2) & 3, rz_ = lane >> 4;   // the lane's row in a brick
+    // children of level l of the node (nx, ny, nz); `rem` are those still to
+    // be looked at, kept per level in lane l of stk while a child's own
+    // children are visited; `up` is the level the climb has reached.  A grid
+    // of at most 4^3 voxels is one brick.
+    int l = 1, up = 1, came = -1;
+    int nx = v0[0] >> 4, ny = v0[1] >> 4, nz = v0[2] >> 4;
+    uint32_t stk_lo = 0u, stk_hi = 0u;
+    unsigned long long rem = 1ull;
+    bool fresh = top > 0;
+    // every round either moves in the tree or loads kN rows per lane and scans
+    // their points
+    while (true) {
+        uint2 e[kN];   // runs of the lane: first point in qs4, points
+        if (cube) {
+#pragma unroll
+            for (int u = 0; u < kN; ++u) {
+                e[u] = make_uint2(0u, 0u);
+                const int it = lane + u * kWave;
+                const int z = it / w, y = it - z * w;
+                // a voxel past 2^31 wraps to a negative index
+                const int vy = (int)((uint32_t)v0[1] + (uint32_t)(y - R)), vz = (int)((uint32_t)v0[2] + (uint32_t)(z - R));
+                const int x0 = max(v0[0] - R, 0), x1 = (int)min((uint32_t)v0[0] + R + 1u, (uint32_t)b.D[0]);
+                if (it < w * w && vy >= 0 && vz >= 0 && vy < b.D[1] && vz < b.D[2]) e[u] = run(x0, x1, vy, vz);
+            }
+        } else {
+            const int cx = 4 * nx + lx, cy = 4 * ny + ly, cz = 4 * nz + lz;
+            if (fresh) {
+                int64_t base = P.t_base;
+                for (int k = 1; k < l; ++k) base += level_cells(b.D[0], b.D[1], b.D[2], k);
+                const int dx = (int)level_dim(b.D[0], l), dy = (int)level_dim(b.D[1], l), dz = (int)level_dim(b.D[2], l);
+                const bool in = cx < dx && cy < dy && cz < dz;
+                const uint8_t f = in ? pyr[base + cx + (int64_t)dx * (cy + (int64_t)dy * cz)] : 0;
+                rem = __ballot(f != 0);
+                if (came >= 0) rem &= ~(1ull << came);
+                came = -1;
+                fresh = false;
+            }
+            float lb = (rem >> lane) & 1ull ? cell_bound(b, l, cx, cy, cz) : INFINITY;
+            float m = __uint_as_float(wave_min_dpp(__float_as_uint(lb)));
+            if (!rem || m * kBoundSlack > best) {   // nothing left here
+                if (top == 0) break;
+                if (l < up) {   // back to the node above
+                    ++l;
+                    nx >>= 2, ny >>= 2, nz >>= 2;
+                    rem = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, l) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, l);
+                    continue;
+                }
+                if (l == top) break;   // everything has been looked at
+                const int sh = 2 * (l + 1);
+                // a node below the top ends at most one voxel row past 2^31
+                const int lo[3] = {nx << sh, ny << sh, nz << sh};
+                const int hi[3] = {(int)min((uint32_t)(nx + 1) << sh, (uint32_t)b.D[0]),
+                                   (int)min((uint32_t)(ny + 1) << sh, (uint32_t)b.D[1]),
+                                   (int)min((uint32_t)(nz + 1) << sh, (uint32_t)b.D[2])};
+                if (outside(lo, hi) * kBoundSlack > best) break;
+                came = (nx & 3) | ((ny & 3) << 2) | ((nz & 3) << 4);
+                nx >>= 2, ny >>= 2, nz >>= 2;
+                up = ++l;
+                fresh = true;
+                continue;
+            }
+            if (l > 1) {   // into the nearest child
+                const int pick = __ffsll((long long)__ballot(((rem >> lane) & 1ull) && lb == m)) - 1;
+                rem &= ~(1ull << pick);
+                stk_lo = lane == l ? (uint32_t)rem : stk_lo;
+                stk_hi = lane == l ? (uint32_t)(rem >> 32) : stk_hi;
+                nx = 4 * nx + (pick & 3), ny = 4 * ny + ((pick >> 2) & 3), nz = 4 * nz + (pick >> 4);
+                --l;
+                fresh = true;
+                continue;
+            }
+            // the nearest kN bricks (one while there is no bound yet): 16 rows
+            // of 4 voxels each, 4 lanes to a row
+#pragma unroll
+            for (int u = 0; u < kN; ++u) {
+                e[u] = make_uint2(0u, 0u);
+                if (u > 0) m = __uint_as_float(wave_min_dpp(__float_as_uint(lb)));
+                if (!rem || m * kBoundSlack > best || (u > 0 && best == INFINITY)) continue;   // uniform
+                const int pick = __ffsll((long long)__ballot(((rem >> lane) & 1ull) && lb == m)) - 1;
+                rem &= ~(1ull << pick);
+                lb = lane == pick ? INFINITY : lb;
+                const int x0 = 4 * (4 * nx + (pick & 3)), vy = 4 * (4 * ny + ((pick >> 2) & 3)) + ry_,
+                          vz = 4 * (4 * nz + (pick >> 4)) + rz_;
+                const int x1 = (int)min((uint32_t)x0 + 4u, (uint32_t)b.D[0]);
+                if (vy < b.D[1] && vz < b.D[2] && !(row_bound(b, x0, x1, vy, vz) * kBoundSlack > best))
+                    e[u] = run(x0, x1, vy, vz);
+            }
         }
-        if (all || R >= kShellMax) return false;
-        // the next cube: large enough for the bound to pass the best found
-        // (its radius in voxels, plus one), or twice as large
-        done_r = R;
-        int next = 2 * R + 1;
-        if (found) next = (int)fminf((float)kShellMax, ceilf(sqrtf(best) * inv) + 1.0f);
-        R = max(R + 1, min(next, kShellMax));
+        // the lane's share of its runs' points (every 4th of a brick's row) as
+        // one flat run, kLoads in flight (a lane past its last point repeats
+        // it); where a lane would scan many, all lanes scan one run at a time
+        const uint32_t first = cube ? 0u : (uint32_t)(lane & 3), sh = cube ? 0u : 2u;
+        uint32_t own[kN], total = 0u;
+#pragma unroll
+        for (int u = 0; u < kN; ++u) {
+            own[u] = e[u].y > first ? (e[u].y - first - 1u >> sh) + 1u : 0u;
+            total += own[u];
+        }
+        if (__ballot(total > kSerialPoints) == 0ull) {
+            for (uint32_t t0 = 0; t0 < total; t0 += kLoads) {
+                float4 q[kLoads];
+#pragma unroll
+                for (int t = 0; t < kLoads; ++t) {
+                    uint32_t f = min(t0 + (uint32_t)t, total - 1u), slot = 0u;
+                    bool found = false;
+#pragma unroll
+                    for (int u = 0; u < kN; ++u) {
+                        const bool here = !found && f < own[u];
+                        slot = here ? e[u].x + first + (f << sh) : slot;
+                        found |= here;
+                        f -= own[u];
+                    }
+                    q[t] = qs4[slot];
+                }
+#pragma unroll
+                for (int t = 0; t < kLoads; ++t) take(q[t]);
+            }
+        } else {
+#pragma unroll 1
+            for (int u = 0; u < kN; ++u) {
+                uint2 eu = e[0];
+#pragma unroll
+                for (int v = 1; v < kN; ++v) eu = u == v ? e[v] : eu;
+                unsigned long long left = __ballot(eu.y > 0u && first == 0u);
+                while (left) {
+                    const int L = __ffsll((long long)left) - 1;
+                    left &= left - 1ull;
+                    const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)eu.x, L);
+                    const uint32_t cn = (uint32_t)__builtin_amdgcn_readlane((int)eu.y, L);
+                    for (uint32_t k = lane; k < cn; k += kLoads * kWave) {
+                        float4 q[kLoads];
+#pragma unroll
+                        for (int t = 0; t < kLoads; ++t) q[t] = qs4[st + min(k + (uint32_t)(t * kWave), cn - 1u)];
+#pragma unroll
+                        for (int t = 0; t < kLoads; ++t) take(q[t]);
+                    }
+                }
+            }
+        }
+        best = __uint_as_float(wave_min_dpp(__float_as_uint(bd)));   // >= 0: bits order as values
+        if (cube) {
+            cube = false;
+            const int lo[3] = {max(v0[0] - R, 0), max(v0[1] - R, 0), max(v0[2] - R, 0)};
+            const int hi[3] = {(int)min((uint32_t)v0[0] + R + 1u, (uint32_t)b.D[0]),
+                               (int)min((uint32_t)v0[1] + R + 1u, (uint32_t)b.D[1]),
+                               (int)min((uint32_t)v0[2] + R + 1u, (uint32_t)b.D[2])};
+            if (outside(lo, hi) * kBoundSlack > best) break;
+        }
     }
+    if (!(best < INFINITY)) return false;
+    // the lowest index among the lanes at the best distance
+    const uint32_t j = wave_min_dpp(bd == best ? bj : 0xFFFFFFFFu);
+    const int owner = __ffsll((long long)__ballot(bd == best && bj == j)) - 1;
+    rd = best;
+    rj = j;
+    rx = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(bx), owner));
+    ry = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(by), owner));
+    rz = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(bz), owner));
+    return true;
 }
 
 // LPQ lanes cooperate on one query: each scans every LPQ-th candidate of the
@@ -302,13 +445,14 @@ __device__ __forceinline__ bool shell_nearest(const PairDev& P, const uint2* __r
 //
 // In registration nn_idx / nn_d2 are optional (null when not asked for): the
 // correspondence and squared distance of each query resolved here (locally,
-// or by the voxel shells of its global search) are written there too; the
+// or by the tree search) are written there too; the
 // solve writes those of the exhaustively searched ones.
 template <int BS, int LPQ, bool kSorted, bool kMom, bool kDirect, int kMode, bool kOne>
 __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd, const BlockJob* __restrict__ jobs,
                                                   const float* __restrict__ px, const float* __restrict__ py,
                                                   const float* __restrict__ pz, const float4* __restrict__ ps4,
                                                   const PairState* __restrict__ st, const uint2* __restrict__ dir,
+                                                  const uint32_t* __restrict__ off, const uint8_t* __restrict__ pyr,
                                                   const float4* __restrict__ qs4, const float4* __restrict__ qsg,
                                                   int32_t* __restrict__ nn_idx, float* __restrict__ nn_d2,
                                                   int32_t* __restrict__ fb_count, int32_t* __restrict__ fb_miss,
@@ -440,13 +584,13 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
         bidx = __float_as_uint(wv.w);
     }
     // The wave resolves its global searches itself, one query at a time, by
-    // the exact shell search over the segments (qsg, whichever layout the
-    // local search reads; not for the exhaustive comparator); those the
-    // shells do not settle are appended to the pair's list for the
-    // exhaustive search, one append per wave, each query at its rank among
-    // the wave's unresolved ones.  Every global search is counted in
+    // the exact tree search over the segments (qsg, whichever layout the
+    // local search reads; not for the exhaustive comparator); those without
+    // a finite distance are appended to the pair's list for the exhaustive
+    // search, one append per wave, each query at its rank among the wave's
+    // unresolved ones.  Every global search is counted in
     // fb_miss.
-    bool shelled = false;
+    bool treed = false;
     unsigned long long left = mmask;
     if (mmask && !all_global) {
         unsigned long long pend = mmask;
@@ -459,10 +603,9 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
             const float lx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sx), L));
             const float ly = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sy), L));
             const float lz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sz), L));
-            if (shell_nearest<kMom ? kShellBatch : kShellBatchNN, kMom ? kShellLoads : kShellLoadsNN,
-                              kMom ? kShellFirst : kShellFirstNN>(P, dir, qsg, lx, ly, lz, rd, rj, rx, ry, rz)) {
+            if (tree_nearest<kMom ? kCubeMin : kCubeMinNN>(P, off, pyr, qsg, lx, ly, lz, rd, rj, rx, ry, rz)) {
                 if (lane == L) {
-                    shelled = true;
+                    treed = true;
                     bd = rd;
                     bidx = rj;
                     bx = rx;
@@ -489,7 +632,7 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
             if (!kMom) nn_idx[gp] = -1 - pos;
         }
     }
-    const bool found = (active && c > 0 && sub == 0) || shelled;
+    const bool found = (active && c > 0 && sub == 0) || treed;
     if (found && (!kMom || nn_idx)) {
         nn_idx[gp] = (int32_t)bidx;
         nn_d2[gp] = bd;
@@ -765,8 +908,8 @@ __global__ void k_copy_fb(const int32_t* __restrict__ fb_count, int32_t* __restr
 
 void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int block, int lpq, bool sorted, bool mom,
                       const float* px, const float* py, const float* pz, const float4* ps4, const PairState* st,
-                      const uint2* dir, const float4* qs4, const float4* qsg, int32_t* nn_idx, float* nn_d2,
-                      int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list, unsigned long long* fb_key, unsigned long long* ctr,
+                      const uint2* dir, const uint32_t* off, const uint8_t* pyr, const float4* qs4, const float4* qsg,
+                      int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list, unsigned long long* fb_key, unsigned long long* ctr,
                       double* part, int all_global, const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m,
                       hipStream_t s)
 {
@@ -778,11 +921,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
 #define VICP_NNS_R(BS, L, SORTED)                                                                                  \
     if (one)                                                                                                       \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
-                     pz, ps4, st, dir, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
                      cap, one_m);                                                                                  \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
-                     pz, ps4, st, dir, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
                      cap, one_m)
 #define VICP_NNS_RL(BS, SORTED)                                     \
     switch (lpq) {                                                  \
@@ -810,11 +953,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
 #define VICP_NNS(BS, L, SORTED, MOM, DIRECT)                                                                       \
     if (one && !DIRECT)                                                                                            \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
-                     pz, ps4, st, dir, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
                      cap, one_m);                                                                                  \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
-                     pz, ps4, st, dir, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
                      cap, one_m)
 #define VICP_NNS_L(BS, SORTED, MOM, DIRECT)                  \
     switch (lpq) {                                           \

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(
     const bool one = gridDim.x == 1;
     const int32_t u0 = one ? 0 : fold_begin[pair], u1 = one ? nunits : fold_begin[pair + 1];
     const int32_t nfb = fb_count[pair];
-    const int32_t nmiss = fb_count[gridDim.x + pair];   // every global search, shell-resolved or listed
+    const int32_t nmiss = fb_count[gridDim.x + pair];   // every global search, resolved in place or listed
     const double prev = S.prev_rmse;
     // the current rotation, the start of the polar refinement: read by every
     // thread (uniform loads, all in flight together; a per-thread condition

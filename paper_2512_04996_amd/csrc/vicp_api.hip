@@ -429,7 +429,7 @@ struct Buf {
 };
 
 struct PairHost {
-    int64_t n = 0, q_base = 0, V = 0, v_base = 0, vm_base = 0;
+    int64_t n = 0, q_base = 0, V = 0, v_base = 0, vm_base = 0, t_base = 0;
     float origin[3] = {0, 0, 0}, inv = 0, voxel = 0;
     int32_t dims[3] = {0, 0, 0};
 };
@@ -497,6 +497,8 @@ struct vicp_grid {
     uint32_t* big_list = nullptr;   // voxels whose segments are sorted whole (fixed grids)
     float4* qs4 = nullptr;
     uint32_t *hist = nullptr, *off = nullptr, *vm = nullptr;
+    uint8_t* pyr = nullptr;   // occupancy pyramids of the pairs, in the words after hist (zeroed with it)
+    int64_t pyr_words = 0;
     uint2* dir = nullptr;   // per voxel: (start in qs4, count | mask), root's entry for a dilated voxel
     BlockJob* jobs_v = nullptr;
     int njobs_v = 0;
@@ -664,6 +666,8 @@ void fill_grid_fields(const PairHost& h, int32_t pad, PairDev& d)
     d.cy = h.origin[1] + 0.5f * (float)h.dims[1] * h.voxel;
     d.cz = h.origin[2] + 0.5f * (float)h.dims[2] * h.voxel;
     d.pad = pad;
+    d.t_base = h.t_base;
+    d.t_top = pyramid_top(h.dims);
 }
 
 void fill_pairdev(const vicp_grid* g, std::vector<PairDev>& pd)
@@ -782,7 +786,7 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
     }
     g->staging = g->take(sizeof(double) * 12 * B, s, L, ok);
     // per pair: the global-search list's length, then (fb_count + B) every
-    // query that needed a global search, shell-resolved or listed
+    // query that needed a global search, resolved in place or listed
     g->fb_count = (int32_t*)g->take(sizeof(int32_t) * 2 * B, s, L, ok);
     g->fb_list = (uint32_t*)g->take(sizeof(uint32_t) * mt1, s, L, ok);
     g->fb_key = (unsigned long long*)g->take(sizeof(unsigned long long) * mt1, s, L, ok);
@@ -896,7 +900,7 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
     {
         ProfScope ps(direct ? "nns_direct" : "nns_local", s, cap, true);
         launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, g->sort_src, mom, px, py,
-                         pz, g->ps4, g->st, g->dir, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2, g->fb_count,
+                         pz, g->ps4, g->st, g->dir, g->off, g->pyr, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2, g->fb_count,
                          g->fb_count + g->B, g->fb_list,
                          g->fb_key, g->ctr, g->npart, all_global ? 1 : 0, direct ? g->dcnt : nullptr, g->dcap,
                          g->search_mode, g->B == 1 ? g->m[0] : -1, s);
@@ -1097,8 +1101,14 @@ int grid_fill_host(vicp_grid* g, const float* qx, const float* qy, const float* 
     }
     if (Vt >= ((int64_t)1 << 31) || words >= ((int64_t)1 << 32))
         return fail(VICP_ERR_GRID_TOO_LARGE, "batch exceeds 2^31 voxels or 2^32 index words");
-    bool same_shape = g->hist != nullptr && Vt == g->V_total;
-    for (int p = 0; p < B && same_shape; ++p) same_shape = pairs[p].V == g->pairs[p].V;
+    // the pyramids' bytes and the dilation's tiles depend on the dims, not on V alone
+    int64_t pyr_bytes = 0;
+    for (int p = 0; p < B; ++p) {
+        pairs[p].t_base = pyr_bytes;
+        pyr_bytes += pyramid_bytes(pairs[p].dims);
+    }
+    bool same_shape = g->hist != nullptr;
+    for (int p = 0; p < B && same_shape; ++p) same_shape = memcmp(pairs[p].dims, g->pairs[p].dims, sizeof(pairs[p].dims)) == 0;
     g->qx = qx;
     g->qy = qy;
     g->qz = qz;
@@ -1128,7 +1138,9 @@ int grid_fill_host(vicp_grid* g, const float* qx, const float* qy, const float* 
         }
         const int tiles = scan_tiles(Vt);
         bool ok = true;
-        g->hist = (uint32_t*)g->take(sizeof(uint32_t) * Vt, s, g->vbufs, ok);
+        g->pyr_words = pyr_bytes / 4;
+        g->hist = (uint32_t*)g->take(sizeof(uint32_t) * (Vt + g->pyr_words), s, g->vbufs, ok);
+        g->pyr = (uint8_t*)(g->hist + Vt);
         g->off = (uint32_t*)g->take(sizeof(uint32_t) * (Vt + 1), s, g->vbufs, ok);
         g->vm = (uint32_t*)g->take(sizeof(uint32_t) * words, s, g->vbufs, ok);
         g->dir = (uint2*)g->take(sizeof(uint2) * Vt, s, g->vbufs, ok);
@@ -1167,11 +1179,11 @@ void clear_for_build(vicp_grid* g, hipStream_t s)
     if (bytes <= sizeof(Blob)) {
         Blob b;
         memcpy(b.w, g->h_pd.data(), bytes);
-        launch_clear4_blob(b, (uint32_t*)g->d_pd, (int)(bytes / 4), g->hist, Vt, g->scan_status, scan_tiles(Vt),
+        launch_clear4_blob(b, (uint32_t*)g->d_pd, (int)(bytes / 4), g->hist, Vt + g->pyr_words, g->scan_status, scan_tiles(Vt),
                            g->scan_ticket, 4, g->err, 4, s);
     } else {
         upload(g->h_pd.data(), bytes, g->d_pd, s);
-        launch_clear4(g->hist, Vt, g->scan_status, scan_tiles(Vt), g->scan_ticket, 4, g->err, 4, s);
+        launch_clear4(g->hist, Vt + g->pyr_words, g->scan_status, scan_tiles(Vt), g->scan_ticket, 4, g->err, 4, s);
     }
 }
 
@@ -1202,7 +1214,7 @@ void queue_build_rest(vicp_grid* g, hipStream_t s, bool cap)
     {
         ProfScope ps("rank_sort", s, cap, true);
         launch_rank_sort(g->qx, g->qy, g->qz, g->d_pd, g->jobs_q, g->njobs_q, g->vox, g->hist, g->off, g->slots,
-                         g->vm, g->qs4, s);
+                         g->vm, g->qs4, g->pyr, s);
     }
 }
 
@@ -1273,12 +1285,12 @@ int grid_fill(vicp_grid* g, const float* qx, const float* qy, const float* qz, h
     {
         ProfScope ps("rank_sort", s, false, true);
         launch_rank_sort(qx, qy, qz, g->d_pd, g->jobs_q, g->njobs_q, g->vox, g->hist, g->off, g->slots, g->vm,
-                         g->qs4, s, seg_sort ? kSegSortMin : 0xFFFFFFFFu);
+                         g->qs4, g->pyr, s, seg_sort ? kSegSortMin : 0xFFFFFFFFu);
     }
     if (seg_sort) {
         ProfScope ps("seg_sort", s, false, true);
         launch_sort_segments(qx, qy, qz, g->d_pd, g->big_list, g->err + 1, g->hist, g->off, g->slots, g->vm, g->qs4,
-                             s);
+                             g->pyr, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(VICP_ERR_HIP, std::string("grid build: ") + hipGetErrorString(e));
@@ -1731,7 +1743,7 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb,
                        (int32_t)njobs256, base);
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
-                     g->qs4, g->qs4, nn_idx, nn_d2, cnt, cnt + 2, fb_list, fb_key, ctr, nullptr, 0, nullptr, 0u, 0, m, s);
+                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, cnt, cnt + 2, fb_list, fb_key, ctr, nullptr, 0, nullptr, 0u, 0, m, s);
     if (!launch_fallback(pd, 1, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, st, cnt, fb_list, fb_key, nullptr, 0,
                          nullptr, nullptr, nullptr, nullptr, s))
         return fail(VICP_ERR_INVALID_ARG, "global-search grid out of range");
@@ -1975,7 +1987,7 @@ int rebuild_register_impl(vicp_grid* g, const float* qx, const float* qy, const 
             f.m[p] = g->m[p];
         }
         uint32_t* z32[6] = {g->hist, g->scan_ticket, g->err, g->sh, g->s_ticket, (uint32_t*)g->sbig};
-        const int64_t n32[6] = {Vt, 4, 4, nb, 4, g->B};
+        const int64_t n32[6] = {Vt + g->pyr_words, 4, 4, nb, 4, g->B};
         for (int k = 0; k < 6; ++k) {
             f.z32[k] = z32[k];
             f.n32[k] = n32[k];
@@ -1984,7 +1996,7 @@ int rebuild_register_impl(vicp_grid* g, const float* qx, const float* qy, const 
         f.n64[0] = scan_tiles(Vt);
         f.z64[1] = g->s_status;
         f.n64[1] = scan_tiles(nb);
-        const int64_t n = std::max(Vt, nb);
+        const int64_t n = std::max(Vt + g->pyr_words, nb);
         const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048));
         ProfScope ps("start_frame", s, cap);
         hipLaunchKernelGGL(k_start_frame, dim3(blocks), dim3(256), 0, s, bl, (uint32_t*)g->d_pd, (int)(pd_bytes / 4), f,
@@ -2012,7 +2024,7 @@ int rebuild_register_impl(vicp_grid* g, const float* qx, const float* qy, const 
     {
         ProfScope ps("rank_pair", s, cap, true);
         launch_rank_pair(g->qx, g->qy, g->qz, g->d_pd, g->jobs_q, g->njobs_q, g->vox, g->hist, g->off, g->slots,
-                         g->vm, g->qs4, pj, np, px, py, pz, g->skey, g->soff, g->sidx, g->sbig, g->ps4, s);
+                         g->vm, g->qs4, g->pyr, pj, np, px, py, pz, g->skey, g->soff, g->sidx, g->sbig, g->ps4, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(VICP_ERR_HIP, std::string("grid build: ") + hipGetErrorString(e));

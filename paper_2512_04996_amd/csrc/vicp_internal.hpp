@@ -11,6 +11,8 @@
 //   qs4          the target points in segment order as float4
 //                (x, y, z, index bits): one coalesced 16-byte
 //                load per candidate in the local search          n_total
+//   pyr          occupancy pyramid of the grid, one byte per cell of
+//                4^l voxels per axis (exact global search)       about V_total / 63
 // Segment v of pair p starts at off[v_base + v] (a global word offset);
 // its points sit in qs4 from off[g] - 2 g (g = v_base + v), because every
 // voxel before g contributes exactly two header words to off[g].
@@ -75,8 +77,51 @@ struct PairDev {
     int64_t s_base;   // first source bucket: V * s_chunks voxel buckets, then ceil(m / kOutChunk) "outside" buckets
     int64_t s_chunks; // index chunks per voxel bucket (1 on fine grids)
     int32_t s_shift;  // a source point's chunk is its index >> s_shift
-    int32_t s_pad;
+    int32_t t_top;    // highest level of the occupancy pyramid (0: every axis has at most 4 voxels, no pyramid)
+    int64_t t_base;   // first byte of the pair's occupancy pyramid
 };
+
+// Occupancy pyramid of a pair's grid: level l (1 .. t_top) has one byte per
+// cell of 4^l voxels along each axis (x fastest), non-zero when a target
+// point lies in the cell; level t_top is the first with at most 4 cells
+// along every axis.  Levels follow each other, level 1 first.
+__host__ __device__ inline uint32_t level_dim(int32_t D, int l)
+{
+    return ((uint32_t)D + ((1u << (2 * l)) - 1u)) >> (2 * l);
+}
+__host__ __device__ inline int64_t level_cells(int32_t Dx, int32_t Dy, int32_t Dz, int l)
+{
+    return (int64_t)level_dim(Dx, l) * level_dim(Dy, l) * level_dim(Dz, l);
+}
+inline int pyramid_top(const int32_t D[3])
+{
+    int l = 0;
+    while (level_dim(D[0], l) > 4 || level_dim(D[1], l) > 4 || level_dim(D[2], l) > 4) ++l;
+    return l;
+}
+// Bytes of a pair's pyramid, rounded up to whole words (they are zeroed as words).
+inline int64_t pyramid_bytes(const int32_t D[3])
+{
+    int64_t b = 0;
+    for (int l = pyramid_top(D); l >= 1; --l) b += level_cells(D[0], D[1], D[2], l);
+    return (b + 3) & ~(int64_t)3;
+}
+
+// Marks the cells of voxel v (pair-local) on every level.  Called once per
+// occupied voxel; several voxels share a cell and store the same byte, so
+// plain stores do.
+__device__ __forceinline__ void mark_occupied(const PairDev& P, uint32_t v, uint8_t* __restrict__ pyr)
+{
+    const uint32_t Dx = (uint32_t)P.Dx, Dy = (uint32_t)P.Dy;
+    const uint32_t x = v % Dx, yz = v / Dx;
+    const uint32_t y = yz % Dy, z = yz / Dy;
+    int64_t b = P.t_base;
+    for (int l = 1; l <= P.t_top; ++l) {
+        const int64_t dx = level_dim(P.Dx, l), dy = level_dim(P.Dy, l), dz = level_dim(P.Dz, l);
+        pyr[b + (x >> (2 * l)) + dx * ((y >> (2 * l)) + dy * (z >> (2 * l)))] = 1;
+        b += dx * dy * dz;
+    }
+}
 
 // A padded grid box whose coordinates all lie within +-kCoordLimit keeps
 // every float32 difference and squared distance between two points inside it
@@ -258,6 +303,21 @@ __device__ __forceinline__ double wave_sum_f64(double x)
                             __builtin_amdgcn_readlane(__double2loint(x), 63));
 }
 
+// Minimum over the 64 lanes, returned to every lane.
+__device__ __forceinline__ uint32_t wave_min_dpp(uint32_t x)
+{
+#define VICP_MIN_STEP(CTRL, ROWS) \
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, CTRL, ROWS, 0xF, false))
+    VICP_MIN_STEP(0x111, 0xF);
+    VICP_MIN_STEP(0x112, 0xF);
+    VICP_MIN_STEP(0x114, 0xF);
+    VICP_MIN_STEP(0x118, 0xF);
+    VICP_MIN_STEP(0x142, 0xA);
+    VICP_MIN_STEP(0x143, 0xC);
+#undef VICP_MIN_STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 // --------------------------------------------------------------------------
 // Rank of e among the c values a[lo .. lo + c): how many are smaller.  Reads
 // 16-byte aligned chunks, eight in flight per round; a must be allocated with
@@ -397,7 +457,7 @@ void launch_place(const PairDev* pd, const BlockJob* jobs, int njobs, const uint
 // launch_sort_segments (pass kSegSortMin when it runs, else UINT32_MAX)
 void launch_rank_sort(const float* qx, const float* qy, const float* qz, const PairDev* pd,
                       const BlockJob* jobs, int njobs, const uint32_t* vox, const uint32_t* hist,
-                      const uint32_t* off, const uint32_t* tmp, uint32_t* vm, float4* qs4,
+                      const uint32_t* off, const uint32_t* tmp, uint32_t* vm, float4* qs4, uint8_t* pyr,
                       hipStream_t s, uint32_t sort_min = 0xFFFFFFFFu);
 // Long segments of a single-pair grid listed by the count: each sorted in
 // LDS (ascending index) by one block, then written to vm and qs4.
@@ -405,7 +465,8 @@ constexpr uint32_t kSegSortMin = 512;
 constexpr uint32_t kSegSortMax = 16384;
 void launch_sort_segments(const float* qx, const float* qy, const float* qz, const PairDev* pd,
                           const uint32_t* big_list, const uint32_t* big_count, const uint32_t* hist,
-                          const uint32_t* off, const uint32_t* tmp, uint32_t* vm, float4* qs4, hipStream_t s);
+                          const uint32_t* off, const uint32_t* tmp, uint32_t* vm, float4* qs4, uint8_t* pyr,
+                          hipStream_t s);
 void launch_clear4(uint32_t* a, int64_t na, unsigned long long* b, int64_t nb, uint32_t* c, int64_t nc, uint32_t* d,
                    int64_t nd, hipStream_t s);
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t count, hipStream_t s);
@@ -434,8 +495,8 @@ void launch_replicate(const PairDev* pd, int64_t V, const uint32_t* state, uint3
 // jobs of block / lpq queries each (the table is not read), else -1
 void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int block, int lpq, bool sorted, bool mom,
                       const float* px, const float* py, const float* pz, const float4* ps4,
-                      const PairState* st, const uint2* dir, const float4* qs4, const float4* qsg,
-                      int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list,
+                      const PairState* st, const uint2* dir, const uint32_t* off, const uint8_t* pyr,
+                      const float4* qs4, const float4* qsg, int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list,
                       unsigned long long* fb_key, unsigned long long* ctr, double* part, int all_global,
                       const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m, hipStream_t s);
 void launch_src_bucket(const PairDev* pd, const BlockJob* jobs, int njobs, const float* px, const float* py,
@@ -463,9 +524,9 @@ void launch_place_pair(const PairDev* pd, const BlockJob* qjobs, int nq, const u
                        const uint32_t* srank, const uint32_t* soff, uint32_t* sidx, hipStream_t s);
 void launch_rank_pair(const float* qx, const float* qy, const float* qz, const PairDev* pd, const BlockJob* qjobs,
                       int nq, const uint32_t* vox, const uint32_t* hist, const uint32_t* off, const uint32_t* tmp,
-                      uint32_t* vm, float4* qs4, const BlockJob* pjobs, int np, const float* px, const float* py,
-                      const float* pz, const uint32_t* skey, const uint32_t* soff, const uint32_t* sidx,
-                      const int32_t* sbig, float4* ps4, hipStream_t s);
+                      uint32_t* vm, float4* qs4, uint8_t* pyr, const BlockJob* pjobs, int np, const float* px,
+                      const float* py, const float* pz, const uint32_t* skey, const uint32_t* soff,
+                      const uint32_t* sidx, const int32_t* sbig, float4* ps4, hipStream_t s);
 // false (nothing launched) for npairs outside [1, kFbMaxPairs]
 bool launch_fallback(const PairDev* pd, int npairs, int grid, const float* qx, const float* qy, const float* qz,
                      const float* px, const float* py, const float* pz, const PairState* st, const int32_t* fb_count,
