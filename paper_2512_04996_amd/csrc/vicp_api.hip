@@ -449,6 +449,18 @@ void make_jobs(const std::vector<int64_t>& counts, int items, std::vector<BlockJ
 constexpr int kNumTables = 6;
 constexpr int kQpb[kNumTables] = {16, 32, 64, 128, 256, 512};
 constexpr int kT256 = 4;   // the 256-per-block table (one lane per point kernels)
+// The resident loop: most units of all pairs (their messages: 1.4 MB) and most
+// blocks.
+constexpr int64_t kLoopMaxUnits = 4096;
+constexpr int kLoopMaxBlocks = 512;
+// The most units a block of the loop takes in turn.  With 196 units of 1024
+// queries on 196 blocks (200,000 points) a step takes 11 us against 18 in three
+// launches; with two units a block (120,000 points at four lanes, a
+// tenth without counterpart) 30 steps take 13.4 ms against 28.8, by its balanced
+// global searches; with seven (1.8M points) it took 3.5 ms
+// for 30 steps against 2.6: the launch-per-step search then has twice the waves
+// in flight on each compute unit, and its launches no longer count.
+constexpr int64_t kLoopRounds = 2;
 // Waves per search block (128, 256 or 512 threads): the search writes one
 // moment record per wave.
 constexpr int kNumWpb = 3;
@@ -529,7 +541,7 @@ struct vicp_grid {
     // in one device block, read back with one copy into pinned host memory
     char* res = nullptr;
     size_t res_bytes = 0;
-    size_t o_rmse = 0, o_ctr = 0, o_fb = 0, o_deg = 0, o_flags = 0;
+    size_t o_rmse = 0, o_ctr = 0, o_fb = 0, o_deg = 0, o_flags = 0, o_abort = 0;
     // pinned host memory mapped for the device: the result block, then the
     // tag of the registration that wrote it (res_gen)
     void* h_res = nullptr;
@@ -572,8 +584,8 @@ struct vicp_grid {
     int32_t* job_begin6 = nullptr;      // per pair, blocks of each source table
     BlockJob* jobs_p[kNumTables] = {};
     int njobs_p[kNumTables] = {};
-    // fold units of the search's per-wave records, per search table and
-    // waves per block (kWpb): units of up to kFoldChunk consecutive records
+    // fold jobs of the search's per-wave records, per search table and waves
+    // per block (kWpb)
     FoldJob* fjobs[kNumTables][kNumWpb] = {};
     int nfjobs[kNumTables][kNumWpb] = {};
     int32_t* fold_begin6 = nullptr;     // per table, waves per block and pair: first fold unit
@@ -593,6 +605,13 @@ struct vicp_grid {
     unsigned long long* s_status = nullptr;
     uint32_t* s_ticket = nullptr;
     std::vector<Buf> ws_bufs;
+
+    // the resident loop's messages, and the last tag used in them (no tag is 0)
+    unsigned long long *loop_msg = nullptr, *loop_pose = nullptr;
+    int64_t loop_units = 0;
+    uint32_t loop_tag = 0;
+    LoopJob* loop_jobs = nullptr;   // a batch's blocks, for loop_lpq lanes per query
+    int loop_lpq = 0, loop_blocks = 0;
 
     // Captured work: the registration (plan + iterations).
     struct Captured {
@@ -730,17 +749,22 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
         make_jobs(m, kQpb[k], jobs[k], &begin);
         begin6.insert(begin6.end(), begin.begin(), begin.end());
         for (int wi = 0; wi < kNumWpb; ++wi) {
-            // pair p's records are [begin[p] * wpb, begin[p + 1] * wpb)
-            const int32_t wpb = kWpb[wi];
+            // pair p's records are the first R from begin[p] * wpb (the waves
+            // of its last block past its last query add nothing)
+            const int32_t wpb = kWpb[wi], lpq = 64 * wpb / kQpb[k];
+            int32_t units = 0;
             fbegin6.push_back(0);
             for (int p = 0; p < B; ++p) {
-                const int32_t r1 = begin[p + 1] * wpb;
-                for (int32_t r = begin[p] * wpb; r < r1; r += kFoldChunk)
-                    folds[k][wi].push_back({p, r, std::min(r + kFoldChunk, r1), 0});
-                fbegin6.push_back((int32_t)folds[k][wi].size());
+                const int32_t R = lpq >= 1 && lpq <= 8 ? (int32_t)wave_records(m[p], lpq) : 0;
+                const int32_t U = (int32_t)record_units(R);
+                // groups in the order of their sums: slice by slice
+                for (int32_t g0 = 0; g0 < U; g0 += kGroupSpan)
+                    for (int32_t u = g0; u < std::min(U, g0 + kUnitSlices); ++u)
+                        folds[k][wi].push_back({p, begin[p] * wpb, R, U, u, units++});
+                fbegin6.push_back(units);
             }
-            max_rec = std::max(max_rec, (size_t)begin[B] * wpb);
-            max_units = std::max(max_units, folds[k][wi].size());
+            if (units) max_rec = std::max(max_rec, (size_t)begin[B] * wpb);
+            max_units = std::max(max_units, (size_t)units);
         }
     }
     const int64_t nb = source_buckets(g, m);
@@ -756,7 +780,8 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
         g->o_fb = g->o_ctr + sizeof(unsigned long long) * 2 * bk;
         g->o_deg = g->o_fb + sizeof(int32_t) * bk;
         g->o_flags = g->o_deg + sizeof(int32_t) * bk;
-        g->res_bytes = a8(g->o_flags + sizeof(int32_t) * B);
+        g->o_abort = a8(g->o_flags + sizeof(int32_t) * B);
+        g->res_bytes = g->o_abort + 8;
         g->res = (char*)g->take(g->res_bytes, s, L, ok);
         if (g->res) {
             g->st = (PairState*)g->res;
@@ -809,6 +834,16 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
     g->ps4 = (float4*)g->take(sizeof(float4) * mt1, s, L, ok);
     g->s_status = (unsigned long long*)g->take(sizeof(unsigned long long) * std::max(stiles, 1), s, L, ok);
     g->s_ticket = (uint32_t*)g->take(sizeof(uint32_t) * 4, s, L, ok);
+    // messages of the finest schedule (8 lanes per query) the loop takes
+    g->loop_units = 0;
+    for (int p = 0; p < B; ++p) g->loop_units += record_units(wave_records(m[p], 8));
+    g->loop_units = std::min<int64_t>(g->loop_units, kLoopMaxUnits);
+    const int64_t loop_words = g->loop_units * kLoopWords + (int64_t)B * kPoseWords;
+    g->loop_msg = (unsigned long long*)g->take(sizeof(unsigned long long) * std::max<int64_t>(loop_words, 1), s, L, ok);
+    g->loop_pose = g->loop_msg + g->loop_units * kLoopWords;
+    g->loop_jobs = (LoopJob*)g->take(sizeof(LoopJob) * kLoopMaxBlocks, s, L, ok);
+    g->loop_lpq = 0;
+    g->loop_tag = 0;
     for (int k = 0; k < kNumTables; ++k) {
         g->jobs_p[k] = (BlockJob*)g->take(sizeof(BlockJob) * std::max<size_t>(jobs[k].size(), 1), s, L, ok);
         g->njobs_p[k] = (int)jobs[k].size();
@@ -840,6 +875,8 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
                             hipMemcpyHostToDevice, s));
     g->job_begin = g->job_begin6 + kT256 * (B + 1);
     launch_fill_u32((uint32_t*)g->fb_count, 0u, 2 * B, s);
+    launch_fill_u64(g->loop_msg, 0ull, loop_words, s);
+    launch_fill_u64((unsigned long long*)(g->res + g->o_abort), 0ull, 1, s);
     VICP_HIP(hipStreamSynchronize(s));
     g->m_total = mt;
     g->K_cap = Kc;
@@ -1797,6 +1834,139 @@ int capture_into(vicp_grid* g, vicp_grid::Captured& c, const std::vector<uintptr
     return VICP_OK;
 }
 
+// ---------------------------------------------------- the resident loop's host side
+
+// One resident loop at a time per device: two that together exceed the device
+// could each hold what the other waits for.  A call that finds it taken runs
+// the launch-per-step form.
+constexpr int kMaxDevices = 64;
+std::mutex g_loop_mu[kMaxDevices];
+
+// Blocks of the loop kernel that fit the device together (0 when unknown).
+int loop_capacity(int dev, int lpq, bool sorted)
+{
+    static std::mutex mu;
+    static int cap[kMaxDevices][4][2];   // 0: not asked yet
+    const int li = lpq == 1 ? 0 : lpq == 2 ? 1 : lpq == 4 ? 2 : 3;
+    std::lock_guard<std::mutex> lk(mu);
+    int& c = cap[dev][li][sorted ? 1 : 0];
+    if (c == 0) {
+        int per = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, loop_kernel(lpq, sorted), loop_threads(), 0) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per < 1 || cus < 1) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        c = std::min(per * cus, kLoopMaxBlocks);
+    }
+    return c;
+}
+
+// Blocks of pair p's U units when every block takes at most r of them.
+int32_t loop_pair_blocks(int64_t U, int64_t r) { return (int32_t)((U + r - 1) / r); }
+
+// The number of loop blocks for the grid's source and schedule, with a batch's
+// table on the device; 0 when the loop does not take it.
+int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
+{
+    const int lpq = g->nns_lpq, B = g->B;
+    std::vector<int64_t> U(B);
+    int64_t total = 0, most = 0;
+    for (int p = 0; p < B; ++p) {
+        U[p] = record_units(wave_records(g->m[p], lpq));
+        total += U[p];
+        most = std::max(most, U[p]);
+    }
+    if (total < 1 || total > g->loop_units || capacity < 1) return 0;
+    // the fewest units per block for which all blocks fit; with more than
+    // kLoopRounds the launch-per-step form, which has more waves in flight, is
+    // the faster
+    int64_t r = std::max<int64_t>(1, (total + capacity - 1) / capacity);
+    auto blocks = [&](int64_t rr) {
+        int64_t n = 0;
+        for (int p = 0; p < B; ++p) n += loop_pair_blocks(U[p], rr);
+        return n;
+    };
+    while (r < most && blocks(r) > capacity) ++r;
+    const int64_t nb = blocks(r);
+    if (nb > capacity || r > kLoopRounds) return 0;
+    for (int p = 0; p < B; ++p)   // a pair on one block keeps its units' sums there
+        if (U[p] > loop_alone_units() && loop_pair_blocks(U[p], r) == 1) return 0;
+    if (B == 1) return (int)nb;
+    if (g->loop_lpq == lpq && g->loop_blocks == (int)nb) return (int)nb;
+    // blocks b, b + 8, ... share an XCD: a pair's blocks go there together,
+    // the largest pairs first, each to the XCD with the most room
+    std::vector<int> order(B);
+    for (int p = 0; p < B; ++p) order[p] = p;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return U[a] > U[b]; });
+    std::vector<LoopJob> jobs((size_t)nb);
+    std::vector<int32_t> base(B);
+    int32_t acc = 0;
+    for (int p = 0; p < B; ++p) {
+        base[p] = acc;
+        acc += (int32_t)U[p];
+    }
+    int next[kXcds];
+    for (int x = 0; x < kXcds; ++x) next[x] = x;
+    for (int p : order) {
+        if (U[p] == 0) continue;
+        const int32_t n = loop_pair_blocks(U[p], r);
+        for (int32_t b = 0, x = -1; b < n; ++b) {
+            if (x < 0 || next[x] >= nb) {
+                x = 0;
+                for (int y = 1; y < kXcds; ++y)
+                    if (next[y] < next[x]) x = y;
+            }
+            jobs[next[x]] = LoopJob{p, b, n, base[p]};
+            next[x] += kXcds;
+        }
+    }
+    upload(jobs.data(), sizeof(LoopJob) * jobs.size(), g->loop_jobs, s);
+    g->loop_lpq = lpq;
+    g->loop_blocks = (int)nb;
+    return (int)nb;
+}
+
+// The loop's launch: K iterations from the state now in g->st on nloop blocks
+// (loop_plan).
+void queue_loop(vicp_grid* g, const float* px, const float* py, const float* pz, int nloop, int K, int early, double eps,
+                int32_t* out_idx, float* out_d2, hipStream_t s)
+{
+    const int B = g->B;
+    if (g->loop_tag > 0xFFFFFFFFu - 200000u) {   // the tags are used up: start again
+        launch_fill_u64(g->loop_msg, 0ull, g->loop_units * kLoopWords + (int64_t)B * kPoseWords, s);
+        launch_fill_u64((unsigned long long*)(g->res + g->o_abort), 0ull, 1, s);
+        g->loop_tag = 0;
+    }
+    LoopArgs a{};
+    a.pd = g->d_pd;
+    a.st = g->st;
+    a.jobs = B == 1 ? nullptr : g->loop_jobs;
+    a.px = px;
+    a.py = py;
+    a.pz = pz;
+    a.ps4 = g->ps4;
+    a.dir = g->dir;
+    a.off = g->off;
+    a.pyr = g->pyr;
+    a.qs4 = g->qs4;
+    a.nn_idx = out_idx;
+    a.nn_d2 = out_d2;
+    a.msg = g->loop_msg;
+    a.pose_msg = g->loop_pose;
+    a.abort_word = (unsigned long long*)(g->res + g->o_abort);
+    a.rmse_hist = g->rmse_hist;
+    a.fb_hist = g->fb_hist;
+    a.deg_hist = g->deg_hist;
+    a.ctr_hist = g->ctr_hist;
+    a.eps = eps;
+    a.tag = g->loop_tag;
+    a.K = K;
+    a.early_stop = early;
+    launch_loop(a, nloop, g->nns_lpq, g->sort_src, s);
+    g->loop_tag += (uint32_t)K;
+}
+
 // The registration's argument checks (none touches the grid).
 int check_register(const vicp_grid* g, const float* px, const float* py, const float* pz,
                    const int64_t* m_per_pair, const vicp_icp_opts* o, const double* Rt_io)
@@ -1825,7 +1995,7 @@ int check_register(const vicp_grid* g, const float* px, const float* py, const f
 // vicp_rebuild_register, on its second stream, which s waits for).
 int register_impl(vicp_grid* g, const float* px, const float* py, const float* pz, const int64_t* m_per_pair,
                   const vicp_icp_opts* o, double* Rt_io, vicp_icp_stats* stats, hipStream_t s,
-                  bool started = false)
+                  bool started = false, bool allow_loop = true)
 {
     int rc = check_grid(g);
     if (rc) return rc;
@@ -1856,9 +2026,20 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
     float* out_d2 = o->nn_d2;
     constexpr const char* kTooMany = "too many pairs for the global search";
     if (!started) queue_start(g, Rt_io, px, py, pz, s);
-    const bool plan = g->sort_src && !started;
+    bool plan = g->sort_src && !started;
     vicp_grid::Captured& cg = g->reg;
-    if (o->use_graph) {
+    int dev = -1;
+    std::unique_lock<std::mutex> loop_lock;
+    int nloop = 0;
+    if (allow_loop && !all_global && !direct && !g_prof.on && !capturing(s) && hipGetDevice(&dev) == hipSuccess &&
+        dev >= 0 && dev < kMaxDevices) {
+        loop_lock = std::unique_lock<std::mutex>(g_loop_mu[dev], std::try_to_lock);
+        if (loop_lock.owns_lock()) nloop = loop_plan(g, loop_capacity(dev, g->nns_lpq, g->sort_src), s);
+    }
+    if (nloop > 0) {
+        if (plan) queue_plan(g, px, py, pz, s, false);
+        queue_loop(g, px, py, pz, nloop, K, early, eps, out_idx, out_d2, s);
+    } else if (o->use_graph) {
         std::vector<uintptr_t> key = {(uintptr_t)px, (uintptr_t)py, (uintptr_t)pz, (uintptr_t)K, (uintptr_t)early,
                                       (uintptr_t)g->nns_block, (uintptr_t)g->nns_lpq, (uintptr_t)g->fb_grid,
                                       (uintptr_t)g->search_mode,
@@ -1902,6 +2083,12 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
     VICP_HIP(wait_tags((const uint32_t*)g->h_res + rwords, npub, 1, g->res_gen, s));
     if (g_prof.on) VICP_HIP(hipStreamSynchronize(s));
     const char* hb = (const char*)g->h_res;
+    if (nloop > 0 && *(const unsigned long long*)(hb + g->o_abort) == (unsigned long long)(g->loop_tag - (uint32_t)K + 1u)) {
+        // the loop gave up (blocks that never met, or a query without a finite
+        // distance): again by the launch-per-step form
+        loop_lock.unlock();
+        return register_impl(g, px, py, pz, m_per_pair, o, Rt_io, stats, s, false, false);
+    }
     const PairState* hst = (const PairState*)hb;
     const double* hr = (const double*)(hb + g->o_rmse);
     const unsigned long long* hc = (const unsigned long long*)(hb + g->o_ctr);
@@ -2356,7 +2543,10 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
     if (rc) return rc;
     if (!m_per_pair) return fail(VICP_ERR_INVALID_ARG, "null pointer");
     if (searches_per_plan < 1) return fail(VICP_ERR_INVALID_ARG, "searches_per_plan must be >= 1");
-    rc = ensure_source(g, m_per_pair, 1, s);
+    // registrations are timed over kTuneIters iterations, single searches alone
+    constexpr int kTuneIters = 8;
+    const bool registers = searches_per_plan > 1;
+    rc = ensure_source(g, m_per_pair, registers ? kTuneIters : 1, s);
     if (rc) return rc;
     if (g->m_total == 0) return VICP_OK;
     if (!px || !py || !pz) return fail(VICP_ERR_INVALID_ARG, "null pointer");
@@ -2375,16 +2565,16 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
     // one sample is kBurst back-to-back runs (launch jitter averages out);
     // the figure is the best of three samples after one untimed
     constexpr int kBurst = 8;
-    auto timed_raw = [&](auto&& work) -> float {
+    auto timed_raw = [&](auto&& work, int burst = kBurst) -> float {
         float best = 1e30f;
         for (int rep = 0; rep < 4; ++rep) {
             (void)hipEventRecord(a, s);
-            for (int r = 0; r < kBurst; ++r) work();
+            for (int r = 0; r < burst; ++r) work();
             (void)hipEventRecord(b, s);
             (void)hipEventSynchronize(b);
             float ms = 0.0f;
             (void)hipEventElapsedTime(&ms, a, b);
-            if (rep > 0) best = std::min(best, ms / kBurst);
+            if (rep > 0) best = std::min(best, ms / burst);
         }
         return best;
     };
@@ -2439,12 +2629,19 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
         g->dil_shape = bs.dil_shape;
         g->ring_block = bs.ring_block;
     }
-    // (3) the search in its registration form at the identity pose
+    // (3) the search: for single searches in its registration form at the
+    // identity pose, for registrations as kTuneIters iterations from there, in
+    // the form the registration would run (the resident loop where it applies,
+    // which has one block size and candidate loop)
     const float plan_ms = timed([&] { queue_plan(g, px, py, pz, s, true); });
     int best_bs = 256, best_lpq = 4, best_fg = g->fb_grid;
     bool best_sorted = true;
     float best = 1e30f;
     int best_mode = 0;
+    int dev = -1;
+    std::unique_lock<std::mutex> loop_lock;
+    if (registers && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices)
+        loop_lock = std::unique_lock<std::mutex>(g_loop_mu[dev], std::try_to_lock);
     for (int sorted = 0; sorted < 2; ++sorted)
         for (int bs : {128, 256, 512})
             for (int lpq : {1, 2, 4, 8})
@@ -2453,8 +2650,22 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
                     g->nns_lpq = lpq;
                     g->sort_src = sorted != 0;
                     g->search_mode = mode;
-                    const float t = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true, true); }) +
-                                    (sorted ? plan_ms / (float)searches_per_plan : 0.0f);
+                    const int nloop = loop_lock.owns_lock() ? loop_plan(g, loop_capacity(dev, lpq, g->sort_src), s) : 0;
+                    if (nloop > 0 && (bs != 128 || mode != 0)) continue;
+                    float t;
+                    if (registers) {
+                        t = timed_raw([&] {
+                                queue_start(g, rt.data(), px, py, pz, s);
+                                if (nloop > 0)
+                                    queue_loop(g, px, py, pz, nloop, kTuneIters, 0, 0.0, nullptr, nullptr, s);
+                                for (int k = 0; k < kTuneIters && nloop == 0; ++k)
+                                    (void)queue_iteration(g, px, py, pz, k, kTuneIters, 0, 0.0, s, true, false, false,
+                                                          nullptr, nullptr);
+                            }, 1) / (float)kTuneIters;
+                    } else {
+                        t = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true, true); });
+                    }
+                    t += sorted ? plan_ms / (float)searches_per_plan : 0.0f;
                     if (t < kMargin * best) {
                         best = t;
                         best_bs = bs;
@@ -2463,6 +2674,11 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
                         best_mode = mode;
                     }
                 }
+    if (loop_lock.owns_lock()) {
+        VICP_HIP(hipStreamSynchronize(s));   // no loop is left running when the device's turn passes on
+        loop_lock.unlock();
+    }
+    queue_start(g, rt.data(), px, py, pz, s);
     g->nns_block = best_bs;
     g->nns_lpq = best_lpq;
     g->sort_src = best_sorted;

@@ -153,13 +153,29 @@ struct BlockJob {
     int32_t start;
 };
 
-// First-level fold of the search's moment records (one per search wave): up
-// to kFoldChunk consecutive records [b0, b1) of one pair.
-constexpr int kFoldChunk = 64;
+// Order in which a pair's R moment records (one per search wave) are summed,
+// whichever kernels do it and whatever their block sizes.  Unit u of
+// U = ceil(R / kUnitRecords) holds the records u, u + U, u + 2 U, ...
+// (neighbouring records, whose queries lie together, go to different units, so
+// global searches that crowd into one part of the source are shared by all
+// blocks); a record past the last counts as zero.  A unit is a tree sum
+// (unit_sum); kGroupUnits units kUnitSlices apart are added in order to a
+// group; slice s adds its groups (those of units s, s + kUnitSlices, ...) in
+// order, and half_sum_f64 adds the slices.
+constexpr int kUnitRecords = 16;
+constexpr int kUnitSlices = 32;
+constexpr int kGroupUnits = 4;
+constexpr int kGroupSpan = kUnitSlices * kGroupUnits;
+inline int64_t wave_records(int64_t m, int lpq) { return (m * lpq + 63) / 64; }
+inline int64_t record_units(int64_t records) { return (records + kUnitRecords - 1) / kUnitRecords; }
+
+// First-level fold: the group of units u, u + kUnitSlices, ... (those below U)
+// of a pair whose R records start at rec0; `out` is its place among all pairs'
+// groups.
 struct FoldJob {
     int32_t pair;
-    int32_t b0, b1;
-    int32_t pad;
+    int32_t rec0, R, U;
+    int32_t u, out;
 };
 
 // Per-pair ICP state on the device.
@@ -205,8 +221,15 @@ __device__ __forceinline__ void transform(const float* __restrict__ R, float x, 
     sz = __builtin_fmaf(R[6], x, __builtin_fmaf(R[7], y, __builtin_fmaf(R[8], z, R[11])));
 }
 
+// The fields of a pair record that a query's voxel and moments need.
+struct GridGeom {
+    float ox, oy, oz, inv, fDx, fDy, fDz, cx, cy, cz;
+    uint32_t Dx, Dy;
+};
+
 // Voxel of a transformed point, or false when it is outside the grid.
-__device__ __forceinline__ bool voxel_of(const PairDev& P, float sx, float sy, float sz, uint32_t& v)
+template <typename G>
+__device__ __forceinline__ bool voxel_of(const G& P, float sx, float sy, float sz, uint32_t& v)
 {
     const float fx = (sx - P.ox) * P.inv;
     const float fy = (sy - P.oy) * P.inv;
@@ -287,6 +310,16 @@ __device__ __forceinline__ uint32_t row_sum_u32(uint32_t x)
     if (STRIDE <= 4) x = dpp_add_u32<0x114, 0xF>(x);
     x = dpp_add_u32<0x118, 0xF>(x);
     return x;
+}
+
+// Sum over each half of the wave in a fixed order, in lanes 31 and 63.
+__device__ __forceinline__ double half_sum_f64(double x)
+{
+    x = dpp_add<0x111, 0xF>(x);   // row_shr:1
+    x = dpp_add<0x112, 0xF>(x);   // row_shr:2
+    x = dpp_add<0x114, 0xF>(x);   // row_shr:4
+    x = dpp_add<0x118, 0xF>(x);   // row_shr:8
+    return dpp_add<0x142, 0xA>(x);   // row_bcast:15 into rows 1 and 3
 }
 
 // Sum over the 64 lanes in a fixed order (an inclusive scan inside each row
@@ -530,7 +563,7 @@ void launch_rank_pair(const float* qx, const float* qy, const float* qz, const P
 // false (nothing launched) for npairs outside [1, kFbMaxPairs]
 bool launch_fallback(const PairDev* pd, int npairs, int grid, const float* qx, const float* qy, const float* qz,
                      const float* px, const float* py, const float* pz, const PairState* st, const int32_t* fb_count,
-                     const uint32_t* fb_list, unsigned long long* fb_key, const FoldJob* fjobs, int nunits,
+                     const uint32_t* fb_list, unsigned long long* fb_key, const FoldJob* fjobs, int nfjobs,
                      const double* part, const unsigned long long* ctr, double* fpart,
                      unsigned long long* fctr, hipStream_t s);
 void launch_fb_finalize(const PairDev* pd, const BlockJob* jobs, int njobs,
@@ -552,6 +585,38 @@ void launch_set_state(const PairDev* pd, PairState* st, const double* rt64, int 
 void launch_check_finite(const PairDev* pd, const BlockJob* jobs, int njobs, const float* px, const float* py,
                          const float* pz, int32_t* flags, hipStream_t s);
 void launch_copy_fb(const int32_t* fb_count, int32_t* out, int npairs, hipStream_t s);
+
+// The registration loop in one resident launch (k_loop.hip).  A block serves
+// one pair's units u0, u0 + stride, ...; the block with u0 = 0 solves.
+struct LoopJob {
+    int32_t pair, u0, stride, unit_base;   // unit_base: the pair's first unit among all pairs' messages
+};
+constexpr int kLoopWords = 2 * (kMoments + 3);   // a unit's message: two tagged words per moment and per counter
+constexpr int kPoseWords = 13;                 // a pose message: 12 float32 words and the stop flag
+struct LoopArgs {
+    const PairDev* pd;
+    PairState* st;
+    const LoopJob* jobs;   // null: a single pair, block b takes units b, b + blocks, ...
+    const float *px, *py, *pz;
+    const float4* ps4;
+    const uint2* dir;
+    const uint32_t* off;
+    const uint8_t* pyr;
+    const float4* qs4;
+    int32_t* nn_idx;
+    float* nn_d2;
+    unsigned long long *msg, *pose_msg, *abort_word;
+    double* rmse_hist;
+    int32_t *fb_hist, *deg_hist;
+    unsigned long long* ctr_hist;
+    double eps;
+    uint32_t tag;   // messages of iteration k carry tag + k + 1
+    int32_t K, early_stop;
+};
+const void* loop_kernel(int lpq, bool sorted);
+int loop_threads();
+int loop_alone_units();   // most units of a pair served by one block
+void launch_loop(const LoopArgs& a, int nblocks, int lpq, bool sorted, hipStream_t s);
 
 // differentiable loss
 void launch_se3(const double* xi, int npairs, PairState* st, double* jl6, int32_t* fb_count, int32_t* flags,
