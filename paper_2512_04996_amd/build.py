@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvicp.so")
-SOURCES = ["k_grid.hip", "k_dilate.hip", "k_nns.hip", "k_solve.hip", "k_loop.hip", "k_loss.hip", "vicp_api.hip"]
+SOURCES = ["k_grid.hip", "k_dilate.hip", "k_nns.hip", "k_solve.hip", "k_loop.hip", "k_exhaustive.hip", "k_loss.hip", "vicp_api.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

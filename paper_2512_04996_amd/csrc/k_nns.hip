@@ -24,8 +24,7 @@
 //
 // Global search (empty undilated voxel or outside the grid): the wave
 // resolves the query itself by an exact search of the occupancy pyramid.
-// Exhaustive search (the comparator, and queries without a finite distance):
-// the query is appended to a per-pair list and a brute force over all targets
+// Exhaustive search (queries without a finite distance): the query is appended to a per-pair list and a brute force over all targets
 // resolves it; partial minima from target tiles merge through a 64-bit
 // atomic minimum of (distance bits << 32 | index), which is order-free, so
 // the result is deterministic.
@@ -87,7 +86,7 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
                                                   uint32_t* __restrict__ fb_list,
                                                   unsigned long long* __restrict__ fb_key,
                                                   unsigned long long* __restrict__ ctr, double* __restrict__ part,
-                                                  int all_global, const uint32_t* __restrict__ dcnt, uint32_t cap,
+                                                  const uint32_t* __restrict__ dcnt, uint32_t cap,
                                                   int64_t one_m)
 {
     static_assert(LPQ == 1 || LPQ == 2 || LPQ == 4 || LPQ == 8, "lanes per query");
@@ -140,9 +139,7 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
     if (active) {
         transform(S.Rtf, x, y, z, sx, sy, sz);
         uint32_t v;
-        // all_global: every query takes the exact global search (the
-        // exhaustive-NNS comparator)
-        if (!all_global && voxel_of(P, sx, sy, sz, v)) {
+        if (voxel_of(P, sx, sy, sz, v)) {
             if (kDirect) {
                 const uint32_t e = dcnt[P.v_base + v];
                 const uint32_t cn = e & ~kMask;
@@ -213,14 +210,13 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
     }
     // The wave resolves its global searches itself, one query at a time, by
     // the exact tree search over the segments (qsg, whichever layout the
-    // local search reads; not for the exhaustive comparator); those without
-    // a finite distance are appended to the pair's list for the exhaustive
+    // local search reads); those without a finite distance are appended to the pair's list for the exhaustive
     // search, one append per wave, each query at its rank among the wave's
     // unresolved ones.  Every global search is counted in
     // fb_miss.
     bool treed = false;
     unsigned long long left = mmask;
-    if (mmask && !all_global) {
+    if (mmask) {
         unsigned long long pend = mmask;
         left = 0ull;
         while (pend) {   // uniform over the wave
@@ -473,7 +469,7 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
                       const float* px, const float* py, const float* pz, const float4* ps4, const PairState* st,
                       const uint2* dir, const uint32_t* off, const uint8_t* pyr, const float4* qs4, const float4* qsg,
                       int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list, unsigned long long* fb_key, unsigned long long* ctr,
-                      double* part, int all_global, const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m,
+                      double* part, const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m,
                       hipStream_t s)
 {
     if (njobs <= 0) return;
@@ -484,11 +480,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
 #define VICP_NNS_R(BS, L, SORTED)                                                                                  \
     if (one)                                                                                                       \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
-                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
                      cap, one_m);                                                                                  \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
-                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
                      cap, one_m)
 #define VICP_NNS_RL(BS, SORTED)                                     \
     switch (lpq) {                                                  \
@@ -516,11 +512,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
 #define VICP_NNS(BS, L, SORTED, MOM, DIRECT)                                                                       \
     if (one && !DIRECT)                                                                                            \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
-                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
                      cap, one_m);                                                                                  \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
-                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, all_global, dcnt,    \
+                     pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
                      cap, one_m)
 #define VICP_NNS_L(BS, SORTED, MOM, DIRECT)                  \
     switch (lpq) {                                           \

@@ -606,6 +606,9 @@ struct vicp_grid {
     uint32_t* s_ticket = nullptr;
     std::vector<Buf> ws_bufs;
 
+    // the exhaustive search's partial minima (null until its first use)
+    uint2* ex_part = nullptr;
+    int ex_splits = 1;
     // the resident loop's messages, and the last tag used in them (no tag is 0)
     unsigned long long *loop_msg = nullptr, *loop_pose = nullptr;
     int64_t loop_units = 0;
@@ -844,6 +847,7 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
     g->loop_jobs = (LoopJob*)g->take(sizeof(LoopJob) * kLoopMaxBlocks, s, L, ok);
     g->loop_lpq = 0;
     g->loop_tag = 0;
+    g->ex_part = nullptr;
     for (int k = 0; k < kNumTables; ++k) {
         g->jobs_p[k] = (BlockJob*)g->take(sizeof(BlockJob) * std::max<size_t>(jobs[k].size(), 1), s, L, ok);
         g->njobs_p[k] = (int)jobs[k].size();
@@ -926,12 +930,11 @@ void queue_start(vicp_grid* g, const double* rt_host, const float* px, const flo
 
 // Correspondence search for every pair at the poses in g->st (Alg. 4).
 // mom: registration form (per-block moment partials; the per-query results
-// only when nn_idx is not null).  all_global: every query takes the exact
-// global search.  direct: search VANICP's monolithic layout instead
+// only when nn_idx is not null).  direct: search VANICP's monolithic layout instead
 // (registration form).  False when the batch is too large for the global
 // search (nothing of it queued).
 bool queue_search(vicp_grid* g, const float* px, const float* py, const float* pz, int32_t* nn_idx, float* nn_d2,
-                  hipStream_t s, bool cap, bool mom, bool all_global = false, bool direct = false)
+                  hipStream_t s, bool cap, bool mom, bool direct = false)
 {
     const int tab = table_of(g->nns_block / g->nns_lpq);
     {
@@ -939,7 +942,7 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
         launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, g->sort_src, mom, px, py,
                          pz, g->ps4, g->st, g->dir, g->off, g->pyr, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2, g->fb_count,
                          g->fb_count + g->B, g->fb_list,
-                         g->fb_key, g->ctr, g->npart, all_global ? 1 : 0, direct ? g->dcnt : nullptr, g->dcap,
+                         g->fb_key, g->ctr, g->npart, direct ? g->dcnt : nullptr, g->dcap,
                          g->search_mode, g->B == 1 ? g->m[0] : -1, s);
     }
     ProfScope ps("fallback", s, cap, true);
@@ -949,15 +952,60 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
                            g->fpart, g->fctr, s);
 }
 
+// The registration form of the search with every query compared with every
+// target, and the fold of its records (one lane per query in blocks of 256,
+// the source in index order).
+bool queue_exhaustive(vicp_grid* g, const float* px, const float* py, const float* pz, int32_t* nn_idx, float* nn_d2,
+                      hipStream_t s, bool cap)
+{
+    if (g->B > kFbMaxPairs) return false;
+    uint2* part = g->ex_part ? g->ex_part : (uint2*)g->fb_key;
+    {
+        ProfScope ps("exhaustive", s, cap, true);
+        launch_exhaustive(g->d_pd, g->B, *std::max_element(g->m.begin(), g->m.end()), g->m_total, g->st, px, py, pz,
+                          g->qx, g->qy, g->qz, part, g->ex_splits, s);
+    }
+    {
+        ProfScope ps("exhaustive_record", s, cap);
+        launch_exhaustive_record(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], g->m_total, g->st, px, py, pz, g->qx,
+                                 g->qy, g->qz, part, g->ex_splits, nn_idx, nn_d2, g->fb_count + g->B, g->npart,
+                                 g->ctr, s);
+    }
+    const int wi = wpb_index(256);
+    ProfScope ps("fallback", s, cap, true);
+    return launch_fallback(g->d_pd, g->B, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, g->st, g->fb_count,
+                           g->fb_list, g->fb_key, g->fjobs[kT256][wi], g->nfjobs[kT256][wi], g->npart, g->ctr,
+                           g->fpart, g->fctr, s);
+}
+
+// The exhaustive search's splits, and the words of their minima: taken with
+// the first such registration of a source (not while a stream is captured,
+// and when there is no memory, one split, whose words are fb_key's).
+void plan_exhaustive(vicp_grid* g, hipStream_t s)
+{
+    if (g->m_total == 0) return;
+    const int most = exhaustive_max_splits(g->m_total);
+    if (most > 1 && !g->ex_part && !capturing(s)) {
+        bool ok = true;
+        g->ex_part = (uint2*)g->take(sizeof(uint2) * (size_t)most * (size_t)g->m_total, s, g->ws_bufs, ok);
+        if (!ok) (void)hipGetLastError();
+    }
+    std::vector<int64_t> n(g->B);
+    for (int p = 0; p < g->B; ++p) n[p] = g->pairs[p].n;
+    g->ex_splits = g->ex_part ? exhaustive_split(g->m.data(), n.data(), g->B, g->m_total, most) : 1;
+}
+
 // One ICP iteration (search, global search with the fold, solve); nn_idx /
 // nn_d2 (optional) receive the iteration's correspondences.
 bool queue_iteration(vicp_grid* g, const float* px, const float* py, const float* pz, int k, int K, int early,
                      double eps, hipStream_t s, bool cap, bool all_global, bool direct, int32_t* nn_idx, float* nn_d2)
 {
-    if (!queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, true, all_global, direct)) return false;
+    if (!(all_global ? queue_exhaustive(g, px, py, pz, nn_idx, nn_d2, s, cap)
+                     : queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, true, direct)))
+        return false;
     ProfScope ps("solve", s, cap, true);
-    const int tab = table_of(g->nns_block / g->nns_lpq);
-    const int wi = wpb_index(g->nns_block);
+    const int tab = all_global ? kT256 : table_of(g->nns_block / g->nns_lpq);
+    const int wi = wpb_index(all_global ? 256 : g->nns_block);
     launch_solve(g->d_pd, g->B, g->fold_begin6 + (tab * kNumWpb + wi) * (g->B + 1), g->nfjobs[tab][wi], g->fpart,
                  g->fctr, g->st,
                  g->fb_count, g->fb_list, g->fb_key, px, py, pz, g->qx, g->qy, g->qz, g->flags, g->rmse_hist,
@@ -1780,7 +1828,7 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb,
                        (int32_t)njobs256, base);
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
-                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, cnt, cnt + 2, fb_list, fb_key, ctr, nullptr, 0, nullptr, 0u, 0, m, s);
+                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, cnt, cnt + 2, fb_list, fb_key, ctr, nullptr, nullptr, 0u, 0, m, s);
     if (!launch_fallback(pd, 1, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, st, cnt, fb_list, fb_key, nullptr, 0,
                          nullptr, nullptr, nullptr, nullptr, s))
         return fail(VICP_ERR_INVALID_ARG, "global-search grid out of range");
@@ -2036,6 +2084,7 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
         loop_lock = std::unique_lock<std::mutex>(g_loop_mu[dev], std::try_to_lock);
         if (loop_lock.owns_lock()) nloop = loop_plan(g, loop_capacity(dev, g->nns_lpq, g->sort_src), s);
     }
+    if (all_global) plan_exhaustive(g, s);
     if (nloop > 0) {
         if (plan) queue_plan(g, px, py, pz, s, false);
         queue_loop(g, px, py, pz, nloop, K, early, eps, out_idx, out_d2, s);

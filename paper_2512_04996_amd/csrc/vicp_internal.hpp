@@ -530,8 +530,25 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
                       const float* px, const float* py, const float* pz, const float4* ps4,
                       const PairState* st, const uint2* dir, const uint32_t* off, const uint8_t* pyr,
                       const float4* qs4, const float4* qsg, int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list,
-                      unsigned long long* fb_key, unsigned long long* ctr, double* part, int all_global,
+                      unsigned long long* fb_key, unsigned long long* ctr, double* part,
                       const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m, hipStream_t s);
+// The search of every query over every target: `part` holds a word per source
+// point (of all pairs: `total`) and split of the targets.  The splits are
+// chosen so that the blocks' rounds on the device's compute units are full:
+// below kExDeep blocks on each, a block's latencies are not hidden; a split
+// costs its block kExCost chunks' time besides its own chunks.
+constexpr int64_t kExWords = 1 << 21;
+constexpr int kExMaxSplits = 256;
+constexpr int64_t kExCus = 256, kExDeep = 4, kExCost = 2;
+int exhaustive_max_splits(int64_t total);
+int exhaustive_split(const int64_t* m, const int64_t* n, int npairs, int64_t total, int max_splits);
+void launch_exhaustive(const PairDev* pd, int npairs, int64_t most_m, int64_t total, const PairState* st,
+                       const float* px, const float* py, const float* pz, const float* qx, const float* qy,
+                       const float* qz, uint2* part, int splits, hipStream_t s);
+void launch_exhaustive_record(const PairDev* pd, const BlockJob* jobs, int njobs, int64_t total, const PairState* st,
+                              const float* px, const float* py, const float* pz, const float* qx, const float* qy,
+                              const float* qz, const uint2* part, int splits, int32_t* nn_idx, float* nn_d2,
+                              int32_t* fb_miss, double* rec, unsigned long long* ctr, hipStream_t s);
 void launch_src_bucket(const PairDev* pd, const BlockJob* jobs, int njobs, const float* px, const float* py,
                        const float* pz, const PairState* st, uint32_t* sh, uint32_t* skey, uint32_t* srank,
                        int32_t* sbig, int32_t* flags, hipStream_t s);
