@@ -148,6 +148,18 @@ __device__ __attribute__((noinline)) bool block_misses(const PairDev* P, const u
     return all;
 }
 
+// crowd_scan, out of line: most searches have no crowded voxel, and inlined its
+// registers would be theirs too.  No position (the largest value): not found.
+__device__ __attribute__((noinline)) uint2 block_crowd(const float4* qs4, uint32_t start, uint32_t c, float sx, float sy,
+                                                       float sz)
+{
+    float bd = INFINITY;
+    uint32_t bk = 0xFFFFFFFFu;
+    if (!crowd_scan(uniform_ptr(qs4), (int64_t)start, c, sx, sy, sz, threadIdx.x & (kWave - 1), bd, bk))
+        bk = 0xFFFFFFFFu;
+    return make_uint2(__float_as_uint(bd), bk);
+}
+
 __device__ __forceinline__ void raise_abort(unsigned long long* word, uint32_t tag)
 {
     __hip_atomic_store(word, (unsigned long long)(tag + 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -251,7 +263,14 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
             const bool dil = in && (ent.y & kMask) != 0u;
             float bd = INFINITY, bx = 0.0f, by = 0.0f, bz = 0.0f;
             uint32_t bk = 0xFFFFFFFFu;
-            if (c > 0u) {
+            bool crowd = false;   // uniform over the wave
+            if (LPQ == 8 && crowded(c)) {
+                const uint2 got = block_crowd(A.qs4, cs, c, sx, sy, sz);
+                crowd = __ballot(got.y == 0xFFFFFFFFu) == 0ull;
+                bd = crowd ? __uint_as_float(got.x) : bd;
+                bk = crowd ? got.y : bk;
+            }
+            if (!crowd && c > 0u) {
                 constexpr int N = LPQ <= 2 ? 8 : 4;
                 const float4* seg = A.qs4 + cs;
                 const uint32_t last = c - 1u;

@@ -161,7 +161,9 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
     float bd = INFINITY;
     uint32_t bj = 0xFFFFFFFFu;
     float bx = 0.0f, by = 0.0f, bz = 0.0f;
-    if (active && c > 0) {
+    bool crowd = false;   // uniform over the wave
+    if (kReload && LPQ == 8 && crowded(c)) crowd = crowd_scan(qs4, cs, c, sx, sy, sz, lane, bd, bj);
+    if (!crowd && active && c > 0) {
         // U candidates per lane per round, all loads issued before the first
         // compare; no serial remainder
         constexpr int U = LPQ <= 2 ? 8 : 4;
