@@ -428,6 +428,16 @@ struct Buf {
     size_t bytes = 0;
 };
 
+// One allocation that holds a set of buffers laid out together: measured by a
+// first pass over the same calls, then taken from.  A set that is laid out
+// again (another voxel or source count) keeps the allocation while it fits and
+// is not four times too large.
+struct Arena {
+    Buf buf;
+    size_t used = 0, need = 0;
+    bool measuring = false;
+};
+
 struct PairHost {
     int64_t n = 0, q_base = 0, V = 0, v_base = 0, vm_base = 0, t_base = 0;
     float origin[3] = {0, 0, 0}, inv = 0, voxel = 0;
@@ -492,8 +502,8 @@ struct vicp_grid {
     std::vector<PairHost> pairs;
     std::vector<float> voxels;
     Mem mem;
-    std::vector<Buf> owned;     // sized by the target point counts (fixed for the grid)
-    std::vector<Buf> vbufs;     // sized by the voxel counts (change when a rebuild changes V)
+    Arena owned;     // sized by the target point counts (fixed for the grid)
+    Arena vbufs;     // sized by the voxel counts (change when a rebuild changes V)
 
     PairDev* d_pd = nullptr;
     uint32_t* err = nullptr;
@@ -604,7 +614,9 @@ struct vicp_grid {
     float4* ps4 = nullptr;
     unsigned long long* s_status = nullptr;
     uint32_t* s_ticket = nullptr;
-    std::vector<Buf> ws_bufs;
+    Arena ws_bufs;   // sized by the source point counts
+    Arena wv_bufs;   // the source buckets', by the voxel counts too
+    Arena ex_bufs;   // the exhaustive search's, from its first use
 
     // the exhaustive search's partial minima (null until its first use)
     uint2* ex_part = nullptr;
@@ -632,27 +644,59 @@ struct vicp_grid {
     Captured reg;
     hipStream_t cap_stream = nullptr;
 
-    void* take(size_t bytes, hipStream_t s, std::vector<Buf>& list, bool& ok)
+    // A buffer of the arena (only its size is noted while it is measured).
+    static void* take(size_t bytes, Arena& a, bool& ok)
     {
-        void* p = mem.get(bytes, s);
-        if (p)
-            list.push_back({p, bytes});
-        else
+        bytes = (std::max<size_t>(bytes, 1) + 255) & ~(size_t)255;
+        if (a.measuring) {
+            a.need += bytes;
+            return nullptr;
+        }
+        if (a.used + bytes > a.buf.bytes) {
             ok = false;
+            return nullptr;
+        }
+        void* p = (char*)a.buf.p + a.used;
+        a.used += bytes;
         return p;
     }
-    void release(std::vector<Buf>& list, hipStream_t s)
+    // Lays the arena out: body(ok) takes its buffers.  An allocation that does
+    // not fit is replaced (by one an eighth larger, so that a count that moves
+    // a little from frame to frame does not replace it each time).
+    template <typename F>
+    bool lay_out(Arena& a, hipStream_t s, F&& body)
     {
-        for (auto& b : list) mem.put(b.p, b.bytes, s);
-        list.clear();
+        bool ok = true;
+        a.measuring = true;
+        a.need = 0;
+        body(ok);
+        a.measuring = false;
+        if (a.buf.bytes < a.need || a.buf.bytes / 4 > a.need) {
+            const size_t spare = a.buf.p ? a.need / 8 : 0;
+            if (a.buf.p && hipStreamSynchronize(s) != hipSuccess) return false;
+            release(a, s);
+            a.buf.bytes = a.need + spare;
+            a.buf.p = mem.get(a.buf.bytes, s);
+            if (!a.buf.p) {
+                a.buf.bytes = 0;
+                return false;
+            }
+        }
+        a.used = 0;
+        body(ok);
+        return ok;
+    }
+    void release(Arena& a, hipStream_t s)
+    {
+        mem.put(a.buf.p, a.buf.bytes, s);
+        a.buf = Buf{};
+        a.used = 0;
     }
     void drop_graph() { reg.drop(); }
     int64_t extra_bytes() const
     {
         int64_t b = 0;
-        for (auto& x : owned) b += (int64_t)x.bytes;
-        for (auto& x : vbufs) b += (int64_t)x.bytes;
-        for (auto& x : ws_bufs) b += (int64_t)x.bytes;
+        for (const Arena* x : {&owned, &vbufs, &ws_bufs, &wv_bufs, &ex_bufs}) b += (int64_t)x->buf.bytes;
         // the paper's accounting: histogram + offsets (8 V) and the dilated voxel index (4 (n + 2V))
         return b - 8 * V_total - 4 * (n_total + 2 * V_total);
     }
@@ -723,6 +767,31 @@ int64_t source_buckets(const vicp_grid* g, const std::vector<int64_t>& m)
     return nb;
 }
 
+// The source buckets' workspaces, which depend on the voxel counts.
+int ensure_buckets(vicp_grid* g, hipStream_t s)
+{
+    const int64_t nb = source_buckets(g, g->m);
+    g->ws_V = -1;
+    const bool ok = g->lay_out(g->wv_bufs, s, [&](bool& ok) {
+        g->sh = (uint32_t*)g->take(sizeof(uint32_t) * nb, g->wv_bufs, ok);
+        g->soff = (uint32_t*)g->take(sizeof(uint32_t) * (nb + 1), g->wv_bufs, ok);
+        g->s_status = (unsigned long long*)g->take(sizeof(unsigned long long) * std::max(scan_tiles(nb), 1), g->wv_bufs, ok);
+    });
+    if (!ok) return fail(VICP_ERR_OOM, "workspace allocation failed");
+    g->ws_V = g->V_total;
+    return VICP_OK;
+}
+
+// A table's place in a block of host tables.
+template <typename T>
+size_t add_table(std::vector<char>& block, const std::vector<T>& t)
+{
+    const size_t at = (block.size() + 255) & ~(size_t)255;
+    block.resize(at + std::max<size_t>(sizeof(T) * t.size(), 1));
+    if (!t.empty()) memcpy(block.data() + at, t.data(), sizeof(T) * t.size());
+    return at;
+}
+
 // (Re)build the source-side device state for a per-pair source layout.
 // Synchronises when the layout changes (rare), so that host staging can be
 // released safely.
@@ -731,10 +800,14 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
     std::vector<int64_t> m(m_per_pair, m_per_pair + g->B);
     for (auto v : m)
         if (v < 0 || v > (int64_t)INT32_MAX) return fail(VICP_ERR_INVALID_ARG, "source size out of range");
-    if (m == g->m && K <= g->K_cap && g->ws_V == g->V_total) return VICP_OK;
-    VICP_HIP(hipStreamSynchronize(s));
+    if (m == g->m && K <= g->K_cap) {
+        if (g->ws_V == g->V_total) return VICP_OK;
+        g->drop_graph();
+        return ensure_buckets(g, s);
+    }
     g->drop_graph();
-    g->release(g->ws_bufs, s);
+    g->release(g->ex_bufs, s);
+    g->ex_part = nullptr;
     g->m.clear();
     g->K_cap = 0;
     g->ws_V = -1;
@@ -770,10 +843,6 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
             max_units = std::max(max_units, (size_t)units);
         }
     }
-    const int64_t nb = source_buckets(g, m);
-    const int stiles = scan_tiles(nb);
-    auto& L = g->ws_bufs;
-    bool ok = true;
     const size_t mt1 = (size_t)std::max<int64_t>(mt, 1);
     {
         auto a8 = [](size_t x) { return (x + 7) & ~(size_t)7; };
@@ -785,15 +854,6 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
         g->o_flags = g->o_deg + sizeof(int32_t) * bk;
         g->o_abort = a8(g->o_flags + sizeof(int32_t) * B);
         g->res_bytes = g->o_abort + 8;
-        g->res = (char*)g->take(g->res_bytes, s, L, ok);
-        if (g->res) {
-            g->st = (PairState*)g->res;
-            g->rmse_hist = (double*)(g->res + g->o_rmse);
-            g->ctr_hist = (unsigned long long*)(g->res + g->o_ctr);
-            g->fb_hist = (int32_t*)(g->res + g->o_fb);
-            g->deg_hist = (int32_t*)(g->res + g->o_deg);
-            g->flags = (int32_t*)(g->res + g->o_flags);
-        }
         if (g->h_res_cap < g->res_bytes) {
             if (g->h_res) (void)hipHostFree(g->h_res);
             g->h_res = nullptr;
@@ -808,84 +868,82 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
                 if (g->h_res) (void)hipHostFree(g->h_res);
                 g->h_res = nullptr;
                 g->d_hres = nullptr;
-                ok = false;
+                return fail(VICP_ERR_OOM, "pinned host allocation failed");
             }
         }
     }
-    g->staging = g->take(sizeof(double) * 12 * B, s, L, ok);
-    // per pair: the global-search list's length, then (fb_count + B) every
-    // query that needed a global search, resolved in place or listed
-    g->fb_count = (int32_t*)g->take(sizeof(int32_t) * 2 * B, s, L, ok);
-    g->fb_list = (uint32_t*)g->take(sizeof(uint32_t) * mt1, s, L, ok);
-    g->fb_key = (unsigned long long*)g->take(sizeof(unsigned long long) * mt1, s, L, ok);
-    g->nn_idx = (int32_t*)g->take(sizeof(int32_t) * mt1, s, L, ok);
-    g->nn_d2 = (float*)g->take(sizeof(float) * mt1, s, L, ok);
-    g->part = (double*)g->take(sizeof(double) * kMoments * std::max<size_t>(jobs[kT256].size(), 1), s, L, ok);
-    g->job_begin6 = (int32_t*)g->take(sizeof(int32_t) * kNumTables * (B + 1), s, L, ok);
-    g->jl6 = (double*)g->take(sizeof(double) * 36 * B, s, L, ok);
-    g->ctr = (unsigned long long*)g->take(sizeof(unsigned long long) * 3 * max_rec, s, L, ok);
-    g->npart = (double*)g->take(sizeof(double) * kMoments * max_rec, s, L, ok);
-    g->fpart = (double*)g->take(sizeof(double) * kMoments * max_units, s, L, ok);
-    g->fctr = (unsigned long long*)g->take(sizeof(unsigned long long) * 2 * max_units, s, L, ok);
-    g->fold_begin6 = (int32_t*)g->take(sizeof(int32_t) * kNumTables * kNumWpb * (B + 1), s, L, ok);
-    g->sh = (uint32_t*)g->take(sizeof(uint32_t) * nb, s, L, ok);
-    g->soff = (uint32_t*)g->take(sizeof(uint32_t) * (nb + 1), s, L, ok);
-    g->skey = (uint32_t*)g->take(sizeof(uint32_t) * mt1, s, L, ok);
-    g->srank = (uint32_t*)g->take(sizeof(uint32_t) * mt1, s, L, ok);
-    g->sidx = (uint32_t*)g->take(sizeof(uint32_t) * (mt1 + 4), s, L, ok);   // +4: rank_in reads 16-byte chunks
-    g->sbig = (int32_t*)g->take(sizeof(int32_t) * B, s, L, ok);
-    g->ps4 = (float4*)g->take(sizeof(float4) * mt1, s, L, ok);
-    g->s_status = (unsigned long long*)g->take(sizeof(unsigned long long) * std::max(stiles, 1), s, L, ok);
-    g->s_ticket = (uint32_t*)g->take(sizeof(uint32_t) * 4, s, L, ok);
     // messages of the finest schedule (8 lanes per query) the loop takes
     g->loop_units = 0;
     for (int p = 0; p < B; ++p) g->loop_units += record_units(wave_records(m[p], 8));
     g->loop_units = std::min<int64_t>(g->loop_units, kLoopMaxUnits);
     const int64_t loop_words = g->loop_units * kLoopWords + (int64_t)B * kPoseWords;
-    g->loop_msg = (unsigned long long*)g->take(sizeof(unsigned long long) * std::max<int64_t>(loop_words, 1), s, L, ok);
-    g->loop_pose = g->loop_msg + g->loop_units * kLoopWords;
-    g->loop_jobs = (LoopJob*)g->take(sizeof(LoopJob) * kLoopMaxBlocks, s, L, ok);
-    g->loop_lpq = 0;
-    g->loop_tag = 0;
-    g->ex_part = nullptr;
+    // all tables in one host block, for one copy
+    std::vector<char> tables;
+    size_t t_jobs[kNumTables], t_folds[kNumTables][kNumWpb];
     for (int k = 0; k < kNumTables; ++k) {
-        g->jobs_p[k] = (BlockJob*)g->take(sizeof(BlockJob) * std::max<size_t>(jobs[k].size(), 1), s, L, ok);
+        t_jobs[k] = add_table(tables, jobs[k]);
         g->njobs_p[k] = (int)jobs[k].size();
         for (int wi = 0; wi < kNumWpb; ++wi) {
-            g->fjobs[k][wi] = (FoldJob*)g->take(sizeof(FoldJob) * std::max<size_t>(folds[k][wi].size(), 1), s, L, ok);
+            t_folds[k][wi] = add_table(tables, folds[k][wi]);
             g->nfjobs[k][wi] = (int)folds[k][wi].size();
         }
     }
-    if (!ok) {
-        g->release(g->ws_bufs, s);
-        return fail(VICP_ERR_OOM, "workspace allocation failed");
+    const size_t t_fbegin = add_table(tables, fbegin6), t_begin = add_table(tables, begin6);
+    char* d_tables = nullptr;
+    const bool ok = g->lay_out(g->ws_bufs, s, [&](bool& ok) {
+    Arena& L = g->ws_bufs;
+    g->res = (char*)g->take(g->res_bytes, L, ok);
+    d_tables = (char*)g->take(tables.size(), L, ok);
+    g->staging = g->take(sizeof(double) * 12 * B, L, ok);
+    // per pair: the global-search list's length, then (fb_count + B) every
+    // query that needed a global search, resolved in place or listed
+    g->fb_count = (int32_t*)g->take(sizeof(int32_t) * 2 * B, L, ok);
+    g->fb_list = (uint32_t*)g->take(sizeof(uint32_t) * mt1, L, ok);
+    g->fb_key = (unsigned long long*)g->take(sizeof(unsigned long long) * mt1, L, ok);
+    g->nn_idx = (int32_t*)g->take(sizeof(int32_t) * mt1, L, ok);
+    g->nn_d2 = (float*)g->take(sizeof(float) * mt1, L, ok);
+    g->part = (double*)g->take(sizeof(double) * kMoments * std::max<size_t>(jobs[kT256].size(), 1), L, ok);
+    g->jl6 = (double*)g->take(sizeof(double) * 36 * B, L, ok);
+    g->ctr = (unsigned long long*)g->take(sizeof(unsigned long long) * 3 * max_rec, L, ok);
+    g->npart = (double*)g->take(sizeof(double) * kMoments * max_rec, L, ok);
+    g->fpart = (double*)g->take(sizeof(double) * kMoments * max_units, L, ok);
+    g->fctr = (unsigned long long*)g->take(sizeof(unsigned long long) * 2 * max_units, L, ok);
+    g->skey = (uint32_t*)g->take(sizeof(uint32_t) * mt1, L, ok);
+    g->srank = (uint32_t*)g->take(sizeof(uint32_t) * mt1, L, ok);
+    g->sidx = (uint32_t*)g->take(sizeof(uint32_t) * (mt1 + 4), L, ok);   // +4: rank_in reads 16-byte chunks
+    g->sbig = (int32_t*)g->take(sizeof(int32_t) * B, L, ok);
+    g->ps4 = (float4*)g->take(sizeof(float4) * mt1, L, ok);
+    g->s_ticket = (uint32_t*)g->take(sizeof(uint32_t) * 4, L, ok);
+    g->loop_msg = (unsigned long long*)g->take(sizeof(unsigned long long) * std::max<int64_t>(loop_words, 1), L, ok);
+    g->loop_jobs = (LoopJob*)g->take(sizeof(LoopJob) * kLoopMaxBlocks, L, ok);
+    });
+    if (!ok) return fail(VICP_ERR_OOM, "workspace allocation failed");
+    g->loop_pose = g->loop_msg + g->loop_units * kLoopWords;
+    g->loop_lpq = 0;
+    g->loop_tag = 0;
+    g->st = (PairState*)g->res;
+    g->rmse_hist = (double*)(g->res + g->o_rmse);
+    g->ctr_hist = (unsigned long long*)(g->res + g->o_ctr);
+    g->fb_hist = (int32_t*)(g->res + g->o_fb);
+    g->deg_hist = (int32_t*)(g->res + g->o_deg);
+    g->flags = (int32_t*)(g->res + g->o_flags);
+    for (int k = 0; k < kNumTables; ++k) {
+        g->jobs_p[k] = (BlockJob*)(d_tables + t_jobs[k]);
+        for (int wi = 0; wi < kNumWpb; ++wi) g->fjobs[k][wi] = (FoldJob*)(d_tables + t_folds[k][wi]);
     }
+    g->fold_begin6 = (int32_t*)(d_tables + t_fbegin);
+    g->job_begin6 = (int32_t*)(d_tables + t_begin);
+    g->job_begin = g->job_begin6 + kT256 * (B + 1);
     g->m = m;
     std::vector<PairDev> pd;
     fill_pairdev(g, pd);
     VICP_HIP(hipMemcpyAsync(g->d_pd, pd.data(), sizeof(PairDev) * B, hipMemcpyHostToDevice, s));
-    for (int k = 0; k < kNumTables; ++k) {
-        if (!jobs[k].empty())
-            VICP_HIP(hipMemcpyAsync(g->jobs_p[k], jobs[k].data(), sizeof(BlockJob) * jobs[k].size(),
-                                    hipMemcpyHostToDevice, s));
-        for (int wi = 0; wi < kNumWpb; ++wi)
-            if (!folds[k][wi].empty())
-                VICP_HIP(hipMemcpyAsync(g->fjobs[k][wi], folds[k][wi].data(), sizeof(FoldJob) * folds[k][wi].size(),
-                                        hipMemcpyHostToDevice, s));
-    }
-    VICP_HIP(hipMemcpyAsync(g->fold_begin6, fbegin6.data(), sizeof(int32_t) * kNumTables * kNumWpb * (B + 1),
-                            hipMemcpyHostToDevice, s));
-    VICP_HIP(hipMemcpyAsync(g->job_begin6, begin6.data(), sizeof(int32_t) * kNumTables * (B + 1),
-                            hipMemcpyHostToDevice, s));
-    g->job_begin = g->job_begin6 + kT256 * (B + 1);
-    launch_fill_u32((uint32_t*)g->fb_count, 0u, 2 * B, s);
-    launch_fill_u64(g->loop_msg, 0ull, loop_words, s);
-    launch_fill_u64((unsigned long long*)(g->res + g->o_abort), 0ull, 1, s);
-    VICP_HIP(hipStreamSynchronize(s));
+    VICP_HIP(hipMemcpyAsync(d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice, s));
+    launch_clear4((uint32_t*)g->fb_count, 2 * B, g->loop_msg, loop_words, (uint32_t*)(g->res + g->o_abort), 2, nullptr, 0, s);
+    VICP_HIP(hipStreamSynchronize(s));   // the host tables go out of scope
     g->m_total = mt;
     g->K_cap = Kc;
-    g->ws_V = g->V_total;
-    return VICP_OK;
+    return ensure_buckets(g, s);
 }
 
 int check_grid(const vicp_grid* g)
@@ -986,8 +1044,9 @@ void plan_exhaustive(vicp_grid* g, hipStream_t s)
     if (g->m_total == 0) return;
     const int most = exhaustive_max_splits(g->m_total);
     if (most > 1 && !g->ex_part && !capturing(s)) {
-        bool ok = true;
-        g->ex_part = (uint2*)g->take(sizeof(uint2) * (size_t)most * (size_t)g->m_total, s, g->ws_bufs, ok);
+        const bool ok = g->lay_out(g->ex_bufs, s, [&](bool& ok) {
+            g->ex_part = (uint2*)g->take(sizeof(uint2) * (size_t)most * (size_t)g->m_total, g->ex_bufs, ok);
+        });
         if (!ok) (void)hipGetLastError();
     }
     std::vector<int64_t> n(g->B);
@@ -1202,13 +1261,9 @@ int grid_fill_host(vicp_grid* g, const float* qx, const float* qy, const float* 
     g->rings_applied = 0;
     if (!same_shape) {
         // voxel-sized buffers follow the new grid; captured work referring to
-        // the old ones is dropped, the source workspace is rebuilt on demand
-        VICP_HIP(hipStreamSynchronize(s));
+        // the old ones is dropped, the source buckets are laid out on demand
         g->drop_graph();
-        g->release(g->ws_bufs, s);
-        g->m.clear();
         g->ws_V = -1;
-        g->release(g->vbufs, s);
         g->V_total = Vt;
         g->vm_words = words;
         std::vector<int64_t> vcount(B);
@@ -1221,34 +1276,38 @@ int grid_fill_host(vicp_grid* g, const float* qx, const float* qy, const float* 
                 tcount[p] = dilate_tiles(sh, pairs[p].dims[0], pairs[p].dims[1], pairs[p].dims[2]);
             make_jobs(tcount, 1, jt[sh], nullptr);
         }
+        std::vector<char> tables;
+        const size_t t_v = add_table(tables, jv);
+        size_t t_t[kDilateShapes];
+        for (int sh = 0; sh < kDilateShapes; ++sh) {
+            t_t[sh] = add_table(tables, jt[sh]);
+            g->njobs_t[sh] = (int)jt[sh].size();
+        }
+        g->njobs_v = (int)jv.size();
         const int tiles = scan_tiles(Vt);
-        bool ok = true;
+        char* d_tables = nullptr;
         g->pyr_words = pyr_bytes / 4;
-        g->hist = (uint32_t*)g->take(sizeof(uint32_t) * (Vt + g->pyr_words), s, g->vbufs, ok);
-        g->pyr = (uint8_t*)(g->hist + Vt);
-        g->off = (uint32_t*)g->take(sizeof(uint32_t) * (Vt + 1), s, g->vbufs, ok);
-        g->vm = (uint32_t*)g->take(sizeof(uint32_t) * words, s, g->vbufs, ok);
-        g->dir = (uint2*)g->take(sizeof(uint2) * Vt, s, g->vbufs, ok);
-        g->jobs_v = (BlockJob*)g->take(sizeof(BlockJob) * jv.size(), s, g->vbufs, ok);
-        for (int sh = 0; sh < kDilateShapes; ++sh)
-            g->jobs_t[sh] = (BlockJob*)g->take(sizeof(BlockJob) * std::max<size_t>(jt[sh].size(), 1), s, g->vbufs, ok);
-        g->scan_status = (unsigned long long*)g->take(sizeof(unsigned long long) * tiles, s, g->vbufs, ok);
-        g->scan_ticket = (uint32_t*)g->take(sizeof(uint32_t) * 4, s, g->vbufs, ok);
-        g->dil_a = (uint32_t*)g->take(sizeof(uint32_t) * Vt, s, g->vbufs, ok);
-        g->dil_b = (uint32_t*)g->take(sizeof(uint32_t) * Vt, s, g->vbufs, ok);
+        const bool ok = g->lay_out(g->vbufs, s, [&](bool& ok) {
+            Arena& L = g->vbufs;
+            g->hist = (uint32_t*)g->take(sizeof(uint32_t) * (Vt + g->pyr_words), L, ok);
+            g->off = (uint32_t*)g->take(sizeof(uint32_t) * (Vt + 1), L, ok);
+            g->vm = (uint32_t*)g->take(sizeof(uint32_t) * words, L, ok);
+            g->dir = (uint2*)g->take(sizeof(uint2) * Vt, L, ok);
+            d_tables = (char*)g->take(tables.size(), L, ok);
+            g->scan_status = (unsigned long long*)g->take(sizeof(unsigned long long) * tiles, L, ok);
+            g->scan_ticket = (uint32_t*)g->take(sizeof(uint32_t) * 4, L, ok);
+            g->dil_a = (uint32_t*)g->take(sizeof(uint32_t) * Vt, L, ok);
+            g->dil_b = (uint32_t*)g->take(sizeof(uint32_t) * Vt, L, ok);
+        });
         if (!ok) {
-            g->release(g->vbufs, s);
             g->hist = nullptr;
             return fail(VICP_ERR_OOM, "grid allocation failed");
         }
-        g->njobs_v = (int)jv.size();
-        VICP_HIP(hipMemcpyAsync(g->jobs_v, jv.data(), sizeof(BlockJob) * jv.size(), hipMemcpyHostToDevice, s));
-        for (int sh = 0; sh < kDilateShapes; ++sh) {
-            g->njobs_t[sh] = (int)jt[sh].size();
-            if (!jt[sh].empty())
-                VICP_HIP(hipMemcpyAsync(g->jobs_t[sh], jt[sh].data(), sizeof(BlockJob) * jt[sh].size(),
-                                        hipMemcpyHostToDevice, s));
-        }
+        g->pyr = (uint8_t*)(g->hist + Vt);
+        g->jobs_v = (BlockJob*)(d_tables + t_v);
+        for (int sh = 0; sh < kDilateShapes; ++sh) g->jobs_t[sh] = (BlockJob*)(d_tables + t_t[sh]);
+        VICP_HIP(hipMemcpyAsync(d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice, s));
+        VICP_HIP(hipStreamSynchronize(s));   // the host tables go out of scope
     }
     fill_pairdev(g, g->h_pd);
     return VICP_OK;
@@ -1468,34 +1527,37 @@ int build_grid_impl(const float* qx, const float* qy, const float* qz, const int
     make_jobs(ncount, 2048, jq8, nullptr);
     make_jobs(ncount, 512, jq512, nullptr);
     make_jobs(ncount, 1024, jq1024, nullptr);
-    bool ok = true;
-    g->d_pd = (PairDev*)g->take(sizeof(PairDev) * npairs, s, g->owned, ok);
-    g->err = (uint32_t*)g->take(sizeof(uint32_t) * 4, s, g->owned, ok);
-    g->jobs_q = (BlockJob*)g->take(sizeof(BlockJob) * jq.size(), s, g->owned, ok);
-    g->jobs_q8 = (BlockJob*)g->take(sizeof(BlockJob) * jq8.size(), s, g->owned, ok);
-    g->jobs_q512 = (BlockJob*)g->take(sizeof(BlockJob) * jq512.size(), s, g->owned, ok);
-    g->jobs_q1024 = (BlockJob*)g->take(sizeof(BlockJob) * jq1024.size(), s, g->owned, ok);
-    g->vox = (uint32_t*)g->take(sizeof(uint32_t) * nt, s, g->owned, ok);
-    g->rank = (uint32_t*)g->take(sizeof(uint32_t) * nt, s, g->owned, ok);
-    g->slots = (uint32_t*)g->take(sizeof(uint32_t) * (nt + 4), s, g->owned, ok);   // +4: rank_in reads 16-byte chunks
-    // the long segments a fixed grid's count lists (at most n / kSegSortMin)
-    g->big_list = (uint32_t*)g->take(sizeof(uint32_t) * (nt / kSegSortMin + 1), s, g->owned, ok);
-    g->qs4 = (float4*)g->take(sizeof(float4) * nt, s, g->owned, ok);
+    std::vector<PairDev> pd;
+    fill_pairdev(g, pd);   // target fields only; the grid fields follow the bounding box
+    std::vector<char> tables;
+    const size_t t_pd = add_table(tables, pd), t_q = add_table(tables, jq), t_q8 = add_table(tables, jq8);
+    const size_t t_512 = add_table(tables, jq512), t_1024 = add_table(tables, jq1024);
+    char* d_tables = nullptr;
+    const bool ok = g->lay_out(g->owned, s, [&](bool& ok) {
+        Arena& L = g->owned;
+        d_tables = (char*)g->take(tables.size(), L, ok);
+        g->err = (uint32_t*)g->take(sizeof(uint32_t) * 4, L, ok);
+        g->vox = (uint32_t*)g->take(sizeof(uint32_t) * nt, L, ok);
+        g->rank = (uint32_t*)g->take(sizeof(uint32_t) * nt, L, ok);
+        g->slots = (uint32_t*)g->take(sizeof(uint32_t) * (nt + 4), L, ok);   // +4: rank_in reads 16-byte chunks
+        // the long segments a fixed grid's count lists (at most n / kSegSortMin)
+        g->big_list = (uint32_t*)g->take(sizeof(uint32_t) * (nt / kSegSortMin + 1), L, ok);
+        g->qs4 = (float4*)g->take(sizeof(float4) * nt, L, ok);
+    });
     if (!ok) return bail(fail(VICP_ERR_OOM, "allocation failed"));
+    g->d_pd = (PairDev*)(d_tables + t_pd);
+    g->jobs_q = (BlockJob*)(d_tables + t_q);
+    g->jobs_q8 = (BlockJob*)(d_tables + t_q8);
+    g->jobs_q512 = (BlockJob*)(d_tables + t_512);
+    g->jobs_q1024 = (BlockJob*)(d_tables + t_1024);
     g->njobs_q = (int)jq.size();
     g->njobs_q8 = (int)jq8.size();
     g->njobs_q512 = (int)jq512.size();
     g->njobs_q1024 = (int)jq1024.size();
     g->h_jobs_q8 = jq8;
-    std::vector<PairDev> pd;
-    fill_pairdev(g, pd);   // target fields only; the grid fields follow the bounding box
-    if (hipMemcpyAsync(g->d_pd, pd.data(), sizeof(PairDev) * npairs, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(g->jobs_q, jq.data(), sizeof(BlockJob) * jq.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(g->jobs_q8, jq8.data(), sizeof(BlockJob) * jq8.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(g->jobs_q512, jq512.data(), sizeof(BlockJob) * jq512.size(), hipMemcpyHostToDevice, s) !=
-            hipSuccess ||
-        hipMemcpyAsync(g->jobs_q1024, jq1024.data(), sizeof(BlockJob) * jq1024.size(), hipMemcpyHostToDevice, s) !=
-            hipSuccess)
+    // (the tables go out of scope: grid_fill waits for work queued after them
+    // or copies its own and synchronises)
+    if (hipMemcpyAsync(d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice, s) != hipSuccess)
         return bail(fail(VICP_ERR_HIP, "upload failed"));
     int rc = grid_fill(g, qx, qy, qz, s);
     if (rc) return bail(rc);
@@ -2425,6 +2487,8 @@ int vicp_grid_free(vicp_grid* g)
     g->drop_graph();
     (void)vicp_direct_free(g);
     if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
+    g->release(g->ex_bufs, nullptr);
+    g->release(g->wv_bufs, nullptr);
     g->release(g->ws_bufs, nullptr);
     g->release(g->vbufs, nullptr);
     g->release(g->owned, nullptr);
