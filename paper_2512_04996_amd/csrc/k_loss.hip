@@ -131,8 +131,7 @@ __global__ __launch_bounds__(256) void k_loss_terms(const PairDev* __restrict__ 
                                                     const float* __restrict__ pz, const float* __restrict__ qx,
                                                     const float* __restrict__ qy, const float* __restrict__ qz,
                                                     const PairState* __restrict__ st,
-                                                    const unsigned long long* __restrict__ fb_key,
-                                                    int32_t* __restrict__ nn_idx, const double* __restrict__ gloss,
+                                                    const int32_t* __restrict__ nn_idx, const double* __restrict__ gloss,
                                                     float* __restrict__ dpx, float* __restrict__ dpy,
                                                     float* __restrict__ dpz, double* __restrict__ part,
                                                     int32_t* __restrict__ flags)
@@ -148,10 +147,6 @@ __global__ __launch_bounds__(256) void k_loss_terms(const PairDev* __restrict__ 
     if (i < P.m) {
         const int64_t gp = P.p_base + i;
         int32_t j = nn_idx[gp];
-        if (j < 0) {
-            j = (int32_t)(uint32_t)(fb_key[P.p_base + (-1 - j)] & 0xFFFFFFFFull);
-            nn_idx[gp] = j;
-        }
         if ((uint32_t)j >= (uint64_t)P.n) {   // unresolved global search (never expected): flag, do not read
             atomicOr(&flags[job.pair], 2);
             j = 0;
@@ -251,11 +246,11 @@ void launch_se3(const double* xi, int npairs, PairState* st, double* jl6, int32_
 
 void launch_loss_terms(const PairDev* pd, const BlockJob* jobs, int njobs, const float* px, const float* py,
                        const float* pz, const float* qx, const float* qy, const float* qz, const PairState* st,
-                       const unsigned long long* fb_key, int32_t* nn_idx, const double* gloss, float* dpx, float* dpy,
+                       const int32_t* nn_idx, const double* gloss, float* dpx, float* dpy,
                        float* dpz, double* part, int32_t* flags, hipStream_t s)
 {
     if (njobs <= 0) return;
-    hipLaunchKernelGGL(k_loss_terms, dim3(njobs), dim3(256), 0, s, pd, jobs, px, py, pz, qx, qy, qz, st, fb_key, nn_idx,
+    hipLaunchKernelGGL(k_loss_terms, dim3(njobs), dim3(256), 0, s, pd, jobs, px, py, pz, qx, qy, qz, st, nn_idx,
                        gloss, dpx, dpy, dpz, part, flags);
 }
 

@@ -30,6 +30,8 @@
 // the result is deterministic.
 #include <math.h>
 
+#include <algorithm>
+
 #include "search_dev.hpp"
 #include "vicp_internal.hpp"
 
@@ -210,12 +212,25 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
         bz = wv.z;
         bidx = __float_as_uint(wv.w);
     }
-    // The wave resolves its global searches itself, one query at a time, by
-    // the exact tree search over the segments (qsg, whichever layout the
-    // local search reads); those without a finite distance are appended to the pair's list for the exhaustive
-    // search, one append per wave, each query at its rank among the wave's
-    // unresolved ones.  Every global search is counted in
-    // fb_miss.
+    // Correspondence form: the wave's queries without a candidate go into its
+    // mask (wave w of job b: word b * kWaves + w), for k_nns_global.
+    if constexpr (!kMom) {
+        if (lane == 0) {
+            ctr[(int64_t)jb * kWaves + w] = mmask;
+            if (mmask && fb_miss) atomicAdd(&fb_miss[job.pair], (int32_t)__popcll(mmask));
+        }
+        if (active && c > 0 && sub == 0) {
+            nn_idx[gp] = (int32_t)bidx;
+            nn_d2[gp] = bd;
+        }
+        return;
+    }
+    // Registration: the wave resolves its global searches itself, one query at
+    // a time, by the exact tree search over the segments (qsg, whichever layout
+    // the local search reads); those without a finite distance are appended to
+    // the pair's list for the exhaustive search, one append per wave, each query
+    // at its rank among the wave's unresolved ones.  Every global search is
+    // counted in fb_miss.
     bool treed = false;
     unsigned long long left = mmask;
     if (mmask) {
@@ -229,7 +244,7 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
             const float lx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sx), L));
             const float ly = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sy), L));
             const float lz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sz), L));
-            if (tree_nearest<kMom ? kCubeMin : kCubeMinNN>(P, off, pyr, qsg, lx, ly, lz, rd, rj, rx, ry, rz)) {
+            if (tree_nearest<kCubeMin>(P, off, pyr, qsg, lx, ly, lz, rd, rj, rx, ry, rz)) {
                 if (lane == L) {
                     treed = true;
                     bd = rd;
@@ -242,12 +257,10 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
                 left |= 1ull << L;
             }
         }
-    }
-    if (mmask) {
         const int leader = __ffsll((long long)mmask) - 1;
         int32_t base = 0;
         if (lane == leader) {
-            if (fb_miss) atomicAdd(&fb_miss[job.pair], (int32_t)__popcll(mmask));
+            atomicAdd(&fb_miss[job.pair], (int32_t)__popcll(mmask));
             if (left) base = atomicAdd(&fb_count[job.pair], (int32_t)__popcll(left));
         }
         base = __shfl(base, leader, kWave);
@@ -255,16 +268,14 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
             const int32_t pos = base + (int32_t)__popcll(left & ((1ull << lane) - 1ull));
             fb_list[P.p_base + pos] = i;
             fb_key[P.p_base + pos] = ~0ull;
-            if (!kMom) nn_idx[gp] = -1 - pos;
         }
     }
     const bool found = (active && c > 0 && sub == 0) || treed;
-    if (found && (!kMom || nn_idx)) {
+    if (found && nn_idx) {
         nn_idx[gp] = (int32_t)bidx;
         nn_d2[gp] = bd;
     }
-    if (!kMom) return;
-    // Registration: one record per wave, the float64 moments of Eq. 1 over
+    // one record per wave, the float64 moments of Eq. 1 over
     // the wave's resolved queries about the grid centre and three exact
     // counters (candidates scanned, dilated lookups, queries sent to the
     // global search).  No block barrier: the waves of a block finish
@@ -439,30 +450,72 @@ __global__ __launch_bounds__(kFbThreads) void k_fallback(const PairDev* __restri
     }
 }
 
-// Writes the global-search results of the listed queries into nn_idx/nn_d2.
-__global__ __launch_bounds__(256) void k_fb_finalize(const PairDev* __restrict__ pd, const BlockJob* __restrict__ jobs,
-                                                     const unsigned long long* __restrict__ fb_key,
-                                                     int32_t* __restrict__ nn_idx, float* __restrict__ nn_d2,
-                                                     int32_t* __restrict__ flags)
+// The correspondence form's global searches.  Block b takes the masks b,
+// b + gridDim.x, ... of the search's waves, so that every block has its share
+// of a region that misses together, lists their queries in LDS, and its waves
+// resolve them one each at a time.  Resolved by the wave that met it, a query
+// waits for the up to 63 before it, and the longest such chain is the launch:
+// the search of a loss over 16 x 40,000 points of which 3 % have no candidate
+// took 155 us, now 27 and this launch (forward and backward 390 -> 257 us in
+// all); 2,000 queries of which 75 miss took 97 us, now 25.  768 blocks of 8
+// waves fill the device; 1536 of 4 waves share less within a block (298 us),
+// 256 of 16 waves as much (259).  A query without a finite distance goes to
+// target 0, infinitely far.
+// Block 0 also hands out the counts.
+constexpr int kGlThreads = 512, kGlBatch = 256;
+constexpr int kGlMaxBlocks = 768;
+__global__ __launch_bounds__(kGlThreads) void k_nns_global(
+    const PairDev* __restrict__ pd, const BlockJob* __restrict__ jobs, int npairs, int nrec, int waves, int lpq,
+    const float* __restrict__ px, const float* __restrict__ py, const float* __restrict__ pz,
+    const PairState* __restrict__ st, const uint32_t* __restrict__ off, const uint8_t* __restrict__ pyr, const float4* __restrict__ qs4, const unsigned long long* __restrict__ mask,
+    const int32_t* __restrict__ fb_miss, int32_t* __restrict__ nn_idx, float* __restrict__ nn_d2,
+    int32_t* __restrict__ n_fallback)
 {
-    const BlockJob job = jobs[blockIdx.x];
-    const PairDev& P = pd[job.pair];
-    const int64_t i = (int64_t)job.start + threadIdx.x;
-    if (i >= P.m) return;
-    const int64_t gp = P.p_base + i;
-    const int32_t j = nn_idx[gp];
-    if (j >= 0) return;
-    const unsigned long long key = fb_key[P.p_base + (-1 - j)];
-    const uint32_t jj = (uint32_t)(key & 0xFFFFFFFFull);
-    if (jj >= (uint64_t)P.n) atomicOr(&flags[job.pair], 2);   // unresolved global search (never expected)
-    nn_idx[gp] = (int32_t)jj;
-    nn_d2[gp] = __uint_as_float((uint32_t)(key >> 32));
-}
-
-__global__ void k_copy_fb(const int32_t* __restrict__ fb_count, int32_t* __restrict__ out, int npairs)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < npairs) out[p] = fb_count[p];
+    __shared__ uint16_t list[kGlBatch * kWave];   // batch slot * 64 + lane
+    __shared__ int32_t count, taken;
+    if (blockIdx.x == 0 && n_fallback)
+        for (int p = threadIdx.x; p < npairs; p += kGlThreads) n_fallback[p] = fb_miss[p];
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int64_t b0 = blockIdx.x; b0 < nrec; b0 += (int64_t)kGlBatch * gridDim.x) {
+        if (threadIdx.x == 0) count = taken = 0;
+        __syncthreads();
+        const int64_t r = b0 + (int64_t)threadIdx.x * gridDim.x;
+        if (threadIdx.x < kGlBatch && r < nrec) {
+            unsigned long long mm = mask[r];
+            if (mm) {
+                int at = atomicAdd(&count, (int32_t)__popcll(mm));
+                for (; mm; mm &= mm - 1ull) list[at++] = (uint16_t)(threadIdx.x * kWave + __ffsll((long long)mm) - 1);
+            }
+        }
+        __syncthreads();
+        const int n = count;
+        while (true) {
+            int e = lane == 0 ? atomicAdd(&taken, 1) : 0;
+            e = __builtin_amdgcn_readfirstlane(e);
+            if (e >= n) break;
+            const int item = __builtin_amdgcn_readfirstlane((int)list[e]);
+            const int64_t rec = b0 + (int64_t)(item / kWave) * gridDim.x;
+            const int64_t job_at = rec / waves;
+            const BlockJob job = jobs[job_at];
+            const PairDev& P = pd[job.pair];
+            const int64_t t = P.p_base + job.start + ((rec - job_at * waves) * kWave + item % kWave) / lpq;
+            float s[3];
+            transform(st[job.pair].Rtf, px[t], py[t], pz[t], s[0], s[1], s[2]);
+            const auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+            float rd, rx, ry, rz;
+            uint32_t rj;
+            if (!tree_nearest<kCubeMinNN>(P, off, pyr, qs4, uniform(s[0]), uniform(s[1]), uniform(s[2]), rd, rj, rx, ry,
+                                          rz)) {
+                rd = INFINITY;
+                rj = 0u;
+            }
+            if (lane == 0) {
+                nn_idx[t] = (int32_t)rj;
+                nn_d2[t] = rd;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 }  // namespace
@@ -546,12 +599,8 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
         } else {
             VICP_NNS_BS(false, true, false)
         }
-    } else {
-        if (sorted) {
-            VICP_NNS_BS(true, false, false)
-        } else {
-            VICP_NNS_BS(false, false, false)
-        }
+    } else {   // correspondences: always in index order
+        VICP_NNS_BS(false, false, false)
     }
 #undef VICP_NNS_BS
 #undef VICP_NNS_L
@@ -570,17 +619,17 @@ bool launch_fallback(const PairDev* pd, int npairs, int grid, const float* qx, c
     return true;
 }
 
-void launch_fb_finalize(const PairDev* pd, const BlockJob* jobs, int njobs, const unsigned long long* fb_key,
-                        int32_t* nn_idx, float* nn_d2, int32_t* flags, hipStream_t s)
+void launch_nns_global(const PairDev* pd, const BlockJob* jobs, int npairs, int njobs, int block, int lpq,
+                       const float* px, const float* py, const float* pz, const PairState* st, const uint32_t* off,
+                       const uint8_t* pyr, const float4* qs4, const unsigned long long* mask, const int32_t* fb_miss,
+                       int32_t* nn_idx, float* nn_d2, int32_t* n_fallback, hipStream_t s)
 {
     if (njobs <= 0) return;
-    hipLaunchKernelGGL(k_fb_finalize, dim3(njobs), dim3(256), 0, s, pd, jobs, fb_key, nn_idx, nn_d2, flags);
-}
-
-void launch_copy_fb(const int32_t* fb_count, int32_t* out, int npairs, hipStream_t s)
-{
-    if (npairs <= 0) return;
-    hipLaunchKernelGGL(k_copy_fb, dim3((npairs + 255) / 256), dim3(256), 0, s, fb_count, out, npairs);
+    const int waves = block / kWave;
+    const int64_t nrec = (int64_t)njobs * waves;
+    const int nb = (int)std::min<int64_t>((nrec + kGlThreads / kWave - 1) / (kGlThreads / kWave), kGlMaxBlocks);
+    launch_timed(k_nns_global, dim3(nb), dim3(kGlThreads), s, pd, jobs, npairs, (int)nrec, waves, lpq, px, py, pz, st,
+                 off, pyr, qs4, mask, fb_miss, nn_idx, nn_d2, n_fallback);
 }
 
 }  // namespace vicp

@@ -970,12 +970,9 @@ void queue_plan(vicp_grid* g, const float* px, const float* py, const float* pz,
 }
 
 // Per-pair state at the given host poses (12 per pair), with the
-// global-search counts and fault flags zeroed, and the source's finiteness
-// check.  Up to kInlinePairs poses travel in the launch itself; the check
-// rides on the bucketing pass when the search buckets the source (that pass
-// then follows).
-void queue_start(vicp_grid* g, const double* rt_host, const float* px, const float* py, const float* pz,
-                 hipStream_t s)
+// global-search counts and fault flags zeroed.  Up to kInlinePairs poses travel
+// in the launch itself.
+void queue_state(vicp_grid* g, const double* rt_host, hipStream_t s)
 {
     if (g->B <= kInlinePairs) {
         launch_set_state_inline(g->d_pd, g->st, rt_host, g->B, g->fb_count, g->flags, s);
@@ -983,31 +980,58 @@ void queue_start(vicp_grid* g, const double* rt_host, const float* px, const flo
         upload(rt_host, sizeof(double) * 12 * g->B, g->staging, s);
         launch_set_state(g->d_pd, g->st, (const double*)g->staging, g->B, g->fb_count, g->flags, s);
     }
+}
+
+// The same and the source's finiteness check, which rides on the bucketing pass
+// when the search buckets the source (that pass then follows).
+void queue_start(vicp_grid* g, const double* rt_host, const float* px, const float* py, const float* pz,
+                 hipStream_t s)
+{
+    queue_state(g, rt_host, s);
     if (!g->sort_src) launch_check_finite(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], px, py, pz, g->flags, s);
 }
 
-// Correspondence search for every pair at the poses in g->st (Alg. 4).
-// mom: registration form (per-block moment partials; the per-query results
-// only when nn_idx is not null).  direct: search VANICP's monolithic layout instead
-// (registration form).  False when the batch is too large for the global
-// search (nothing of it queued).
+// Registration search for every pair at the poses in g->st (Alg. 4): the
+// moment records, their fold, and the per-query results when nn_idx is not
+// null.  direct: search VANICP's monolithic layout instead.  False when the
+// batch is too large for the global search (nothing of it queued).
 bool queue_search(vicp_grid* g, const float* px, const float* py, const float* pz, int32_t* nn_idx, float* nn_d2,
-                  hipStream_t s, bool cap, bool mom, bool direct = false)
+                  hipStream_t s, bool cap, bool direct = false)
 {
     const int tab = table_of(g->nns_block / g->nns_lpq);
     {
         ProfScope ps(direct ? "nns_direct" : "nns_local", s, cap, true);
-        launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, g->sort_src, mom, px, py,
-                         pz, g->ps4, g->st, g->dir, g->off, g->pyr, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2, g->fb_count,
-                         g->fb_count + g->B, g->fb_list,
-                         g->fb_key, g->ctr, g->npart, direct ? g->dcnt : nullptr, g->dcap,
-                         g->search_mode, g->B == 1 ? g->m[0] : -1, s);
+        launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, g->sort_src, true, px, py,
+                         pz, g->ps4, g->st, g->dir, g->off, g->pyr, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2,
+                         g->fb_count, g->fb_count + g->B, g->fb_list, g->fb_key, g->ctr, g->npart,
+                         direct ? g->dcnt : nullptr, g->dcap, g->search_mode, g->B == 1 ? g->m[0] : -1, s);
     }
     ProfScope ps("fallback", s, cap, true);
     return launch_fallback(g->d_pd, g->B, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, g->st, g->fb_count,
-                           g->fb_list, g->fb_key, mom ? g->fjobs[tab][wpb_index(g->nns_block)] : nullptr,
-                           g->nfjobs[tab][wpb_index(g->nns_block)], g->npart, g->ctr,
-                           g->fpart, g->fctr, s);
+                           g->fb_list, g->fb_key, g->fjobs[tab][wpb_index(g->nns_block)],
+                           g->nfjobs[tab][wpb_index(g->nns_block)], g->npart, g->ctr, g->fpart, g->fctr, s);
+}
+
+// The correspondences of every pair at the poses in g->st and (unless null)
+// each pair's count of global searches.  Over the source in index order,
+// whatever the schedule: bucketing it takes five launches, more than it saves
+// one search (a room of 226,000 points: 26 us against 57 with 200,000 queries,
+// 47 against 238 with a million in random order; a surface whose global
+// searches crowd: 25 against 43 with 2,000, 320 against 294 with a million).
+void queue_correspondences(vicp_grid* g, const float* px, const float* py, const float* pz, int32_t* nn_idx, float* nn_d2,
+                           int32_t* n_fallback, hipStream_t s, bool cap)
+{
+    const int tab = table_of(g->nns_block / g->nns_lpq);
+    int32_t* miss = n_fallback ? g->fb_count + g->B : nullptr;
+    {
+        ProfScope ps("nns_local", s, cap, true);
+        launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, false, false, px, py, pz,
+                         g->ps4, g->st, g->dir, g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, miss, nullptr,
+                         nullptr, g->ctr, nullptr, nullptr, 0u, 0, g->B == 1 ? g->m[0] : -1, s);
+    }
+    ProfScope ps("nns_global", s, cap, true);
+    launch_nns_global(g->d_pd, g->jobs_p[tab], g->B, g->njobs_p[tab], g->nns_block, g->nns_lpq, px, py, pz, g->st, g->off,
+                      g->pyr, g->qs4, g->ctr, miss, nn_idx, nn_d2, n_fallback, s);
 }
 
 // The registration form of the search with every query compared with every
@@ -1060,7 +1084,7 @@ bool queue_iteration(vicp_grid* g, const float* px, const float* py, const float
                      double eps, hipStream_t s, bool cap, bool all_global, bool direct, int32_t* nn_idx, float* nn_d2)
 {
     if (!(all_global ? queue_exhaustive(g, px, py, pz, nn_idx, nn_d2, s, cap)
-                     : queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, true, direct)))
+                     : queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, direct)))
         return false;
     ProfScope ps("solve", s, cap, true);
     const int tab = all_global ? kT256 : table_of(g->nns_block / g->nns_lpq);
@@ -1727,15 +1751,8 @@ int vicp_nns_batched(const vicp_grid* gc, const float* px, const float* py, cons
     const bool cap = capturing(s);
     std::vector<double> rt64(12 * g->B);
     for (int i = 0; i < 12 * g->B; ++i) rt64[i] = (double)Rt[i];
-    queue_start(g, rt64.data(), px, py, pz, s);
-    if (g->sort_src) queue_plan(g, px, py, pz, s, cap);
-    if (!queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, false))
-        return fail(VICP_ERR_INVALID_ARG, "too many pairs for the global search");
-    {
-        ProfScope ps("fb_finalize", s, cap);
-        launch_fb_finalize(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], g->fb_key, nn_idx, nn_d2, g->flags, s);
-    }
-    if (n_fallback) launch_copy_fb(g->fb_count + g->B, n_fallback, g->B, s);
+    queue_state(g, rt64.data(), s);
+    queue_correspondences(g, px, py, pz, nn_idx, nn_d2, n_fallback, s, cap);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(VICP_ERR_HIP, std::string("nns: ") + hipGetErrorString(e));
     return VICP_OK;
@@ -1814,7 +1831,7 @@ struct NaSetup {
 // One launch prepares the search: the pair record and pose, the global-search
 // count and fault flags at zero, and the two block tables (search blocks of
 // qpb queries, result blocks of 256 points).
-__global__ void k_noalloc_setup(NaSetup a, int32_t njobs, int32_t qpb, int32_t njobs256, unsigned char* base)
+__global__ void k_noalloc_setup(NaSetup a, int32_t njobs, int32_t qpb, unsigned char* base)
 {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (tid == 0) {
@@ -1831,15 +1848,10 @@ __global__ void k_noalloc_setup(NaSetup a, int32_t njobs, int32_t qpb, int32_t n
         S.status = 0;
         S.rot_ok = 0;
         int32_t* cnt = reinterpret_cast<int32_t*>(base + kNaOffCnt);
-        cnt[0] = 0;   // global-search list length
-        cnt[1] = 0;   // fault flags
         cnt[2] = 0;   // queries that needed a global search
     }
     BlockJob* jobs = reinterpret_cast<BlockJob*>(base + kNaOffJobs);
-    BlockJob* jobs256 = reinterpret_cast<BlockJob*>(base + kNaOffJobs256);
     for (int64_t j = tid; j < njobs; j += (int64_t)gridDim.x * blockDim.x) jobs[j] = BlockJob{0, (int32_t)(j * qpb)};
-    for (int64_t j = tid; j < njobs256; j += (int64_t)gridDim.x * blockDim.x)
-        jobs256[j] = BlockJob{0, (int32_t)(j * 256)};
 }
 
 }  // namespace
@@ -1871,7 +1883,7 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     // the grid's search schedule, over the source in index order (bucketing
     // the source would need the grid's workspace)
     const int qpb = g->nns_block / g->nns_lpq;
-    const int64_t njobs = (m + qpb - 1) / qpb, njobs256 = (m + 255) / 256;
+    const int64_t njobs = (m + qpb - 1) / qpb;
     NaSetup a{};
     fill_grid_fields(g->pairs[0], g->pad, a.pd);
     a.pd.p_base = 0;
@@ -1882,20 +1894,15 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     const PairDev* pd = reinterpret_cast<const PairDev*>(base + kNaOffPd);
     PairState* st = reinterpret_cast<PairState*>(base + kNaOffSt);
     const BlockJob* jobs = reinterpret_cast<const BlockJob*>(base + kNaOffJobs);
-    const BlockJob* jobs256 = reinterpret_cast<const BlockJob*>(base + kNaOffJobs256);
-    unsigned long long* ctr = reinterpret_cast<unsigned long long*>(base + kNaOffCtr);
-    uint32_t* fb_list = reinterpret_cast<uint32_t*>(base + kNaOffList);
-    unsigned long long* fb_key = reinterpret_cast<unsigned long long*>(base + kNaOffKey);
+    // a word per wave of the search: at most m / 8 + 8
+    unsigned long long* mask = reinterpret_cast<unsigned long long*>(base + kNaOffKey);
     const int setup_blocks = (int)std::min<int64_t>((njobs + 255) / 256, 256);
-    hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb,
-                       (int32_t)njobs256, base);
+    hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb, base);
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
-                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, cnt, cnt + 2, fb_list, fb_key, ctr, nullptr, nullptr, 0u, 0, m, s);
-    if (!launch_fallback(pd, 1, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, st, cnt, fb_list, fb_key, nullptr, 0,
-                         nullptr, nullptr, nullptr, nullptr, s))
-        return fail(VICP_ERR_INVALID_ARG, "global-search grid out of range");
-    launch_fb_finalize(pd, jobs256, (int)njobs256, fb_key, nn_idx, nn_d2, cnt + 1, s);
-    if (n_fallback) launch_copy_fb(cnt + 2, n_fallback, 1, s);
+                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, cnt + 2, nullptr, nullptr, mask, nullptr,
+                     nullptr, 0u, 0, m, s);
+    launch_nns_global(pd, jobs, 1, (int)njobs, g->nns_block, g->nns_lpq, px, py, pz, st, g->off, g->pyr, g->qs4, mask,
+                      cnt + 2, nn_idx, nn_d2, n_fallback, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(VICP_ERR_HIP, std::string("nns_noalloc: ") + hipGetErrorString(e));
     return VICP_OK;
@@ -2373,9 +2380,7 @@ static int p2p_common(vicp_grid* g, const float* px, const float* py, const floa
     if (g->m_total > 0 && (!px || !py || !pz)) return fail(VICP_ERR_INVALID_ARG, "null pointer");
     const bool cap = capturing(s);
     launch_se3(xi, g->B, g->st, g->jl6, g->fb_count, g->flags, s);
-    if (g->sort_src) queue_plan(g, px, py, pz, s, cap);
-    if (!queue_search(g, px, py, pz, g->nn_idx, g->nn_d2, s, cap, false))
-        return fail(VICP_ERR_INVALID_ARG, "too many pairs for the global search");
+    queue_correspondences(g, px, py, pz, g->nn_idx, g->nn_d2, nullptr, s, cap);
     return VICP_OK;
 }
 
@@ -2390,8 +2395,8 @@ int vicp_p2p_loss_fwd(const vicp_grid* gc, const float* px, const float* py, con
     const bool cap = capturing(s);
     {
         ProfScope ps("loss_terms", s, cap);
-        launch_loss_terms(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], px, py, pz, g->qx, g->qy, g->qz, g->st, g->fb_key,
-                          g->nn_idx, nullptr, nullptr, nullptr, nullptr, g->part, g->flags, s);
+        launch_loss_terms(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], px, py, pz, g->qx, g->qy, g->qz, g->st, g->nn_idx,
+                          nullptr, nullptr, nullptr, nullptr, g->part, g->flags, s);
     }
     launch_loss_finish(g->d_pd, g->B, g->job_begin, g->part, g->jl6, nullptr, loss, nullptr, s);
     hipError_t e = hipGetLastError();
@@ -2412,8 +2417,8 @@ int vicp_p2p_loss_bwd(const vicp_grid* gc, const float* px, const float* py, con
     const bool cap = capturing(s);
     {
         ProfScope ps("loss_terms", s, cap);
-        launch_loss_terms(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], px, py, pz, g->qx, g->qy, g->qz, g->st, g->fb_key,
-                          g->nn_idx, gloss, dpx, dpy, dpz, g->part, g->flags, s);
+        launch_loss_terms(g->d_pd, g->jobs_p[kT256], g->njobs_p[kT256], px, py, pz, g->qx, g->qy, g->qz, g->st, g->nn_idx,
+                          gloss, dpx, dpy, dpz, g->part, g->flags, s);
     }
     launch_loss_finish(g->d_pd, g->B, g->job_begin, g->part, g->jl6, gloss, nullptr, dxi, s);
     hipError_t e = hipGetLastError();
@@ -2776,7 +2781,7 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
                                                           nullptr, nullptr);
                             }, 1) / (float)kTuneIters;
                     } else {
-                        t = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true, true); });
+                        t = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true); });
                     }
                     t += sorted ? plan_ms / (float)searches_per_plan : 0.0f;
                     if (t < kMargin * best) {
@@ -2803,7 +2808,7 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
         best = 1e30f;
         for (int fg : {64, 128, 256, 512, 1024}) {
             g->fb_grid = fg;
-            const float t0 = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true, true); });
+            const float t0 = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true); });
             const float t1 = timed_raw([&] {
                 hipLaunchKernelGGL(k_synthetic_misses, dim3(g->B), dim3(256), 0, s, g->d_pd, g->B, g->fb_count,
                                    g->fb_list, g->fb_key);

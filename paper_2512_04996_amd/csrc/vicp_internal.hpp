@@ -583,9 +583,10 @@ bool launch_fallback(const PairDev* pd, int npairs, int grid, const float* qx, c
                      const uint32_t* fb_list, unsigned long long* fb_key, const FoldJob* fjobs, int nfjobs,
                      const double* part, const unsigned long long* ctr, double* fpart,
                      unsigned long long* fctr, hipStream_t s);
-void launch_fb_finalize(const PairDev* pd, const BlockJob* jobs, int njobs,
-                        const unsigned long long* fb_key, int32_t* nn_idx, float* nn_d2,
-                        int32_t* flags, hipStream_t s);
+void launch_nns_global(const PairDev* pd, const BlockJob* jobs, int npairs, int njobs, int block, int lpq,
+                       const float* px, const float* py, const float* pz, const PairState* st, const uint32_t* off,
+                       const uint8_t* pyr, const float4* qs4, const unsigned long long* mask, const int32_t* fb_miss,
+                       int32_t* nn_idx, float* nn_d2, int32_t* n_fallback, hipStream_t s);
 void launch_solve(const PairDev* pd, int npairs, const int32_t* fold_begin, int32_t nunits, const double* fpart,
                   const unsigned long long* fctr, PairState* st, int32_t* fb_count, const uint32_t* fb_list,
                   const unsigned long long* fb_key, const float* px, const float* py, const float* pz,
@@ -601,7 +602,6 @@ void launch_set_state(const PairDev* pd, PairState* st, const double* rt64, int 
                       int32_t* flags, hipStream_t s);
 void launch_check_finite(const PairDev* pd, const BlockJob* jobs, int njobs, const float* px, const float* py,
                          const float* pz, int32_t* flags, hipStream_t s);
-void launch_copy_fb(const int32_t* fb_count, int32_t* out, int npairs, hipStream_t s);
 
 // The registration loop in one resident launch (k_loop.hip).  A block serves
 // one pair's units u0, u0 + stride, ...; the block with u0 = 0 solves.
@@ -640,9 +640,8 @@ void launch_se3(const double* xi, int npairs, PairState* st, double* jl6, int32_
                 hipStream_t s);
 void launch_loss_terms(const PairDev* pd, const BlockJob* jobs, int njobs, const float* px,
                        const float* py, const float* pz, const float* qx, const float* qy,
-                       const float* qz, const PairState* st, const unsigned long long* fb_key,
-                       int32_t* nn_idx, const double* gloss, float* dpx, float* dpy, float* dpz,
-                       double* part, int32_t* flags, hipStream_t s);
+                       const float* qz, const PairState* st, const int32_t* nn_idx, const double* gloss,
+                       float* dpx, float* dpy, float* dpz, double* part, int32_t* flags, hipStream_t s);
 void launch_loss_finish(const PairDev* pd, int npairs, const int32_t* job_begin,
                         const double* part, const double* jl6, const double* gloss,
                         double* loss, double* dxi, hipStream_t s);
