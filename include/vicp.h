@@ -99,7 +99,9 @@ typedef struct vicp_icp_opts {
     int32_t max_iter;   /* K >= 0 */
     double rmse_eps;    /* stop when |RMSE_k - RMSE_{k-1}| < rmse_eps (k >= 1) ... */
     int32_t early_stop; /* ... only if non-zero; 0 runs exactly K iterations */
-    int32_t use_graph;  /* non-zero: capture the K iterations once in a hipGraph and replay it */
+    int32_t use_graph;  /* non-zero: capture the K iterations once in a hipGraph and replay it, where they
+                            do not run in one launch (sources of up to two units of 16 waves per
+                            compute unit do) */
     int32_t global_only; /* non-zero: every query takes the exact global search (ICP with exhaustive
                             NNS, the "Brute" comparator of Table 2); the grid is not consulted */
     int32_t layout;      /* 0: the segmented, offset-addressed layout (Alg. 2-4); 1: VANICP's
@@ -168,8 +170,8 @@ int vicp_build_grid_fixed(const float* qx, const float* qy, const float* qz, int
 /* Refills an existing grid from a new target with the same per-pair point
  * counts (e.g. the next frame of a stream): the bounding box, grid
  * specification, counts, offsets and segments are recomputed exactly as by
- * vicp_build_grid, while allocations, work tables and captured graphs are
- * reused when the voxel counts are unchanged.  The grid is left undilated:
+ * vicp_build_grid, while allocations are reused when the new voxel counts fit
+ * them, and work tables and captured graphs when the shape is unchanged.  The grid is left undilated:
  * call vicp_dilate again.  Waits once for the device (bounding box).
  * Errors as vicp_build_grid; STATE for a grid that was never built.  After a
  * rebuild fails once the new bounding box is known (a target point outside a
@@ -246,8 +248,8 @@ int vicp_nns_batched(const vicp_grid* g, const float* px, const float* py, const
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): vicp_nns
- * with every intermediate (the pose, the work tables, the global-search list
- * and its keys, the per-block counters) in one fixed device array that the
+ * with every intermediate (the pose, the work tables, the search waves' masks
+ * of queries for the global search) in one fixed device array that the
  * library holds on each GPU it runs on until the process ends
  * (14,713,600 bytes, sized for VICP_NOALLOC_MAX_QUERIES source points),
  * instead of the grid's workspace.  Same arguments, outputs and results as vicp_nns (bit for bit:
