@@ -89,23 +89,26 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
                                                   unsigned long long* __restrict__ fb_key,
                                                   unsigned long long* __restrict__ ctr, double* __restrict__ part,
                                                   const uint32_t* __restrict__ dcnt, uint32_t cap,
-                                                  int64_t one_m)
+                                                  int64_t one_m, int early)
 {
     static_assert(LPQ == 1 || LPQ == 2 || LPQ == 4 || LPQ == 8, "lanes per query");
     constexpr bool kReload = kMode == 1;
     static_assert(kMode == 0 || kMode == 1, "search mode");
     static_assert(!kReload || (kMom && !kDirect), "position tracking needs index-ordered segments");
     constexpr int kWaves = BS / kWave;
-    // A batched registration gives each XCD one contiguous eighth of the
-    // jobs, whole pairs, so that an L2 holds its pairs' directories and
-    // segments (the 64-pair batch: 3.66 against 4.2 ms).  A single pair, and
-    // the correspondence form, whose pairs' global searches can crowd into
-    // one eighth, keep the rotating chunks.
-    const int jb = (kMom && !kOne) ? xcd_slab((int)blockIdx.x, (int)gridDim.x)
-                                   : xcd_job((int)blockIdx.x, (int)gridDim.x);
+    // A batch gives each XCD one contiguous eighth of the jobs, whole pairs, so
+    // that an L2 holds its pairs' directories and segments (64 pairs: 3.66
+    // against 4.2 ms; the loss over 16 pairs: 242 against 257 us).  A single
+    // pair keeps the rotating chunks.
+    const int jb = kOne ? xcd_job((int)blockIdx.x, (int)gridDim.x) : xcd_slab((int)blockIdx.x, (int)gridDim.x);
     const BlockJob job = kOne ? BlockJob{0, jb * (BS / LPQ)} : jobs[jb];
     const PairDev& P = pd[job.pair];
     const PairState& S = st[job.pair];
+    // where pairs can stop early, a finished one's blocks end here: 30 launches
+    // behind the stop of a 200,000-point run took 12.4 us each, now 3.3 (the run
+    // 2.70 -> 2.37 ms).  Only there, as the test delays the loads below by the
+    // flag's latency.
+    if (kMom && early && S.done) return;
     const int sub = threadIdx.x % LPQ;
     const int64_t t = (int64_t)job.start + threadIdx.x / LPQ;
     const bool inrange = t < (kOne ? one_m : P.m);
@@ -525,7 +528,7 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
                       const uint2* dir, const uint32_t* off, const uint8_t* pyr, const float4* qs4, const float4* qsg,
                       int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list, unsigned long long* fb_key, unsigned long long* ctr,
                       double* part, const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m,
-                      hipStream_t s)
+                      int early, hipStream_t s)
 {
     if (njobs <= 0) return;
     const bool one = one_m >= 0;
@@ -536,11 +539,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
     if (one)                                                                                                       \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m);                                                                                  \
+                     cap, one_m, early);                                                                                  \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m)
+                     cap, one_m, early)
 #define VICP_NNS_RL(BS, SORTED)                                     \
     switch (lpq) {                                                  \
     case 1: VICP_NNS_R(BS, 1, SORTED); break;                       \
@@ -568,11 +571,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
     if (one && !DIRECT)                                                                                            \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m);                                                                                  \
+                     cap, one_m, early);                                                                                  \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m)
+                     cap, one_m, early)
 #define VICP_NNS_L(BS, SORTED, MOM, DIRECT)                  \
     switch (lpq) {                                           \
     case 2: VICP_NNS(BS, 2, SORTED, MOM, DIRECT); break;     \

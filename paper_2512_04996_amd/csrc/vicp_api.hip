@@ -996,7 +996,7 @@ void queue_start(vicp_grid* g, const double* rt_host, const float* px, const flo
 // null.  direct: search VANICP's monolithic layout instead.  False when the
 // batch is too large for the global search (nothing of it queued).
 bool queue_search(vicp_grid* g, const float* px, const float* py, const float* pz, int32_t* nn_idx, float* nn_d2,
-                  hipStream_t s, bool cap, bool direct = false)
+                  hipStream_t s, bool cap, bool direct = false, int early = 0)
 {
     const int tab = table_of(g->nns_block / g->nns_lpq);
     {
@@ -1004,7 +1004,7 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
         launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, g->sort_src, true, px, py,
                          pz, g->ps4, g->st, g->dir, g->off, g->pyr, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2,
                          g->fb_count, g->fb_count + g->B, g->fb_list, g->fb_key, g->ctr, g->npart,
-                         direct ? g->dcnt : nullptr, g->dcap, g->search_mode, g->B == 1 ? g->m[0] : -1, s);
+                         direct ? g->dcnt : nullptr, g->dcap, g->search_mode, g->B == 1 ? g->m[0] : -1, early, s);
     }
     ProfScope ps("fallback", s, cap, true);
     return launch_fallback(g->d_pd, g->B, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, g->st, g->fb_count,
@@ -1027,7 +1027,7 @@ void queue_correspondences(vicp_grid* g, const float* px, const float* py, const
         ProfScope ps("nns_local", s, cap, true);
         launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, false, false, px, py, pz,
                          g->ps4, g->st, g->dir, g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, miss, nullptr,
-                         nullptr, g->ctr, nullptr, nullptr, 0u, 0, g->B == 1 ? g->m[0] : -1, s);
+                         nullptr, g->ctr, nullptr, nullptr, 0u, 0, g->B == 1 ? g->m[0] : -1, 0, s);
     }
     ProfScope ps("nns_global", s, cap, true);
     launch_nns_global(g->d_pd, g->jobs_p[tab], g->B, g->njobs_p[tab], g->nns_block, g->nns_lpq, px, py, pz, g->st, g->off,
@@ -1084,7 +1084,7 @@ bool queue_iteration(vicp_grid* g, const float* px, const float* py, const float
                      double eps, hipStream_t s, bool cap, bool all_global, bool direct, int32_t* nn_idx, float* nn_d2)
 {
     if (!(all_global ? queue_exhaustive(g, px, py, pz, nn_idx, nn_d2, s, cap)
-                     : queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, direct)))
+                     : queue_search(g, px, py, pz, nn_idx, nn_d2, s, cap, direct, early)))
         return false;
     ProfScope ps("solve", s, cap, true);
     const int tab = all_global ? kT256 : table_of(g->nns_block / g->nns_lpq);
@@ -1900,7 +1900,7 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb, base);
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
                      g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, cnt + 2, nullptr, nullptr, mask, nullptr,
-                     nullptr, 0u, 0, m, s);
+                     nullptr, 0u, 0, m, 0, s);
     launch_nns_global(pd, jobs, 1, (int)njobs, g->nns_block, g->nns_lpq, px, py, pz, st, g->off, g->pyr, g->qs4, mask,
                       cnt + 2, nn_idx, nn_d2, n_fallback, s);
     hipError_t e = hipGetLastError();

@@ -531,7 +531,7 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
                       const PairState* st, const uint2* dir, const uint32_t* off, const uint8_t* pyr,
                       const float4* qs4, const float4* qsg, int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list,
                       unsigned long long* fb_key, unsigned long long* ctr, double* part,
-                      const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m, hipStream_t s);
+                      const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m, int early, hipStream_t s);
 // The search of every query over every target: `part` holds a word per source
 // point (of all pairs: `total`) and split of the targets.  The splits are
 // chosen so that the blocks' rounds on the device's compute units are full:
