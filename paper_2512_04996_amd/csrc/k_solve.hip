@@ -71,6 +71,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(
     PairState& S = st[pair];
     const PairDev& P = pd[pair];
     const int done = S.done;
+    // uniform; only where pairs can stop early, as it delays the loads below (a
+    // run that stops after 20 of 50 steps 2.37 -> 2.24 ms)
+    if (early_stop && done) return;
     // a single pair owns every group: its range needs no table load
     const bool one = gridDim.x == 1;
     const int32_t u0 = one ? 0 : fold_begin[pair], u1 = one ? nunits : fold_begin[pair + 1];
@@ -112,9 +115,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(
         if (last && j >= kMoments && j < kMoments + 2) ctot[j - kMoments] = (unsigned long long)sm;
     }
     __syncthreads();
-    // tested after the fold, whose loads do not depend on it, so that the
-    // flag's latency overlaps theirs (a finished pair's fold units hold
-    // stale sums that are never used)
+    // a pair without source points, done from the start: tested after the
+    // fold, whose loads do not depend on it, so that the flag's latency
+    // overlaps theirs (its groups' sums are never used)
     if (done) return;   // uniform over the block
     const double cen[3] = {P.cx, P.cy, P.cz};
     if (nfb > 0) {   // uniform over the block
