@@ -366,6 +366,11 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
                     st_tagged(out + 1, tag, (uint32_t)__double2hiint(sum));
                 }
             }
+            // the next unit's waves list misses and write records only once
+            // wave 0 has read this unit's, and every wave its count of misses;
+            // after the last unit the gather's or the next pose's barrier
+            // orders them
+            if (u + job.stride < U) __syncthreads();
         }
         if (!solver) continue;
         // the pair's units, kGather at a time: their words as they arrive, then
