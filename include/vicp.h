@@ -286,6 +286,18 @@ int vicp_register_batched(const vicp_grid* g, const float* px, const float* py, 
                           const int64_t* m_per_pair, const vicp_icp_opts* opts, double* Rt_io,
                           vicp_icp_stats* stats, hipStream_t stream);
 
+/* How the grid's last registration (vicp_register, vicp_register_batched or
+ * vicp_rebuild_register) ran: all iterations in one launch, a launch sequence
+ * per iteration, or the latter after the one launch handed over (a query
+ * without a finite distance, or blocks that did not meet).  NONE before the
+ * first, and after one without iterations or source points.  Every form gives
+ * the same results. */
+#define VICP_FORM_NONE 0
+#define VICP_FORM_LOOP 1
+#define VICP_FORM_STEPS 2
+#define VICP_FORM_HANDED_OVER 3
+int vicp_last_form(const vicp_grid* g, int32_t* form);
+
 /* The next frame in one call: vicp_grid_rebuild(qx, qy, qz), vicp_dilate(rings)
  * and vicp_register_batched(px, ...) in turn, with the same results, errors
  * and waits.  When the schedule buckets the source (Alg. 4's queries sorted

@@ -19,6 +19,7 @@ ERR_HIP = -4
 ERR_STATE = -5
 ERR_NONFINITE = -6
 ERR_DEGENERATE = -7
+FORM_NONE, FORM_LOOP, FORM_STEPS, FORM_HANDED_OVER = range(4)
 MASK_BIT = 0x80000000
 NOALLOC_MAX_QUERIES = 1 << 20
 
@@ -75,6 +76,7 @@ SYMBOLS = {
                                 C.POINTER(C.c_double), C.POINTER(IcpStats), C.c_void_p]),
     "vicp_register_batched": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(C.c_int64),
                                         C.POINTER(IcpOpts), C.POINTER(C.c_double), C.POINTER(IcpStats), C.c_void_p]),
+    "vicp_last_form": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32)]),
     "vicp_rebuild_register": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p,
                                         C.c_void_p, C.c_void_p, C.POINTER(C.c_int64), C.POINTER(IcpOpts),
                                         C.POINTER(C.c_double), C.POINTER(IcpStats), C.c_void_p]),

@@ -221,6 +221,15 @@ class Grid:
         return self._register(p, max_iter, rmse_eps, early_stop, use_graph, Rt0, m_per_pair, raise_degenerate,
                               global_only, layout, correspondences)
 
+    @property
+    def last_form(self) -> int:
+        """How the last registration ran: ``_lib.FORM_LOOP`` (all iterations in
+        one launch), ``FORM_STEPS`` (launches per iteration),
+        ``FORM_HANDED_OVER`` (the latter after the former) or ``FORM_NONE``."""
+        f = C.c_int32()
+        check(lib().vicp_last_form(self.handle, C.byref(f)), "vicp_last_form")
+        return f.value
+
     def rebuild_register(self, q: torch.Tensor, rings: int, p: torch.Tensor, max_iter: int, **kw) -> IcpResult:
         """rebuild(q), dilate(rings) and register(p, max_iter, **kw) in one
         call, with the same results; the refill's count, scan, scatter and

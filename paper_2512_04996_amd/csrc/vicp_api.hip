@@ -627,6 +627,7 @@ struct vicp_grid {
     uint32_t loop_tag = 0;
     LoopJob* loop_jobs = nullptr;   // a batch's blocks, for loop_lpq lanes per query
     int loop_lpq = 0, loop_blocks = 0;
+    int32_t last_form = VICP_FORM_NONE;   // how the last registration ran
 
     // Captured work: the registration (plan + iterations).
     struct Captured {
@@ -1630,6 +1631,13 @@ int vicp_grid_rebuild(vicp_grid* g, const float* qx, const float* qy, const floa
 
 int vicp_grid_npairs(const vicp_grid* g) { return g ? g->B : 0; }
 
+int vicp_last_form(const vicp_grid* g, int32_t* form)
+{
+    if (!g || !form) return fail(VICP_ERR_INVALID_ARG, "null pointer");
+    *form = g->last_form;
+    return VICP_OK;
+}
+
 int vicp_set_build_options(vicp_grid* g, int32_t host_offsets, int32_t packed_hash)
 {
     if (!g) return fail(VICP_ERR_INVALID_ARG, "null grid");
@@ -2127,6 +2135,7 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
             stats[p].degenerate = 0;
         }
     const int K = o->max_iter;
+    g->last_form = VICP_FORM_NONE;
     if (mt == 0 || K == 0) return ensure_source(g, m_per_pair, 1, s);
     if (!px || !py || !pz) return fail(VICP_ERR_INVALID_ARG, "null pointer");
     rc = ensure_source(g, m_per_pair, K, s);
@@ -2154,6 +2163,7 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
         if (loop_lock.owns_lock()) nloop = loop_plan(g, loop_capacity(dev, g->nns_lpq, g->sort_src), s);
     }
     if (all_global) plan_exhaustive(g, s);
+    g->last_form = nloop > 0 ? VICP_FORM_LOOP : (allow_loop ? VICP_FORM_STEPS : VICP_FORM_HANDED_OVER);
     if (nloop > 0) {
         if (plan) queue_plan(g, px, py, pz, s, false);
         queue_loop(g, px, py, pz, nloop, K, early, eps, out_idx, out_d2, s);
