@@ -83,11 +83,11 @@ struct LoopShared {
 
 // Eq. 1's solve from the totals in LDS: the pose Rt (in: the previous one), or
 // false when the rotation cannot be refined from the previous one (nearly
-// degenerate sums, a turn of over 90 degrees): the loop then gives up, and the
-// launch-per-step form, whose solve has the registers for the SVD, takes over.
+// planar or degenerate sums, a turn of over 90 degrees): loop_solve_svd then.
 // The rotation goes through LDS, so that the sums are read again for the
 // translation instead of being held in registers through the refinement.
-__device__ __forceinline__ bool loop_solve(LoopShared& sh, bool rot_ok)
+template <SolveStep kStep>
+__device__ __forceinline__ bool solve_totals(LoopShared& sh, bool rot_ok)
 {
     {
         double t[kMoments], Rp[9], R[9];
@@ -95,7 +95,7 @@ __device__ __forceinline__ bool loop_solve(LoopShared& sh, bool rot_ok)
         for (int j = 0; j < kMoments; ++j) t[j] = sh.tot[j];
 #pragma unroll
         for (int j = 0; j < 9; ++j) Rp[j] = sh.Rt[j];
-        if (!kabsch_rotation<true>(t, Rp, rot_ok, R)) return false;
+        if (!kabsch_rotation<kStep>(t, Rp, rot_ok, R)) return false;
 #pragma unroll
         for (int j = 0; j < 9; ++j) sh.Rt[j] = R[j];
     }
@@ -111,6 +111,13 @@ __device__ __forceinline__ bool loop_solve(LoopShared& sh, bool rot_ok)
 #pragma unroll
     for (int j = 0; j < 3; ++j) sh.Rt[9 + j] = tr[j];
     return true;
+}
+
+// The solve without the refinement, out of line, so that its registers are not
+// the loop's: false (pose untouched) when the sums do not determine a rotation.
+__device__ __attribute__((noinline, cold)) bool loop_solve_svd(LoopShared* sh)
+{
+    return solve_totals<kAfterRefine>(*sh, false);
 }
 
 template <typename T>
@@ -431,12 +438,12 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
         if (w == 0) {
             if (lane == 0) {
                 const double n = sh.tot[kMoments - 1], rmse = n > 0.0 ? sqrt(sh.tot[17] / n) : 0.0;
-                if (loop_solve(sh, rot_ok)) {
+                const bool ok = solve_totals<kRefine>(sh, rot_ok) || loop_solve_svd(&sh);
+                if (ok) {
                     for (int j = 0; j < 12; ++j) sh.pose[j] = (float)sh.Rt[j];
                     rot_ok = true;
                 } else {
-                    sh.stop = 1;
-                    raise_abort(B->abort_word, A.tag);
+                    S.degenerate += 1;   // the pose is kept
                 }
                 const bool end = B->early_stop && k >= 1 && fabs(rmse - prev) < B->eps;
                 prev = rmse;
@@ -444,7 +451,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
                 const int64_t h = (int64_t)job.pair * B->K + k;
                 B->rmse_hist[h] = rmse;
                 B->fb_hist[h] = (int32_t)sh.tot[kMoments + 2];
-                B->deg_hist[h] = 0;
+                B->deg_hist[h] = ok ? 0 : 1;
                 B->ctr_hist[2 * h] = (unsigned long long)sh.tot[kMoments];
                 B->ctr_hist[2 * h + 1] = (unsigned long long)sh.tot[kMoments + 1];
                 if (end || k == B->K - 1) {

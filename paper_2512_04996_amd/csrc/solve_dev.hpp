@@ -257,8 +257,10 @@ __host__ __device__ bool polar_refine(const double A[3][3], double scale, const 
 // Rprev (row-major, may be null): the previous rotation, from which the polar
 // factor is refined; prev_orth says it is known to be orthogonal (a previous
 // solve's result), otherwise it is checked here.  In two halves: the rotation
-// R (row-major; kRefineOnly: false also where the refinement does not apply),
-template <bool kRefineOnly>
+// R (row-major; the refinement can be asked for alone, false also where it does
+// not apply, and what follows it alone where it does not),
+enum SolveStep { kSolveAll, kRefine, kAfterRefine };
+template <SolveStep kStep>
 __host__ __device__ __forceinline__ bool kabsch_rotation(const double* mom, const double* Rprev, bool prev_orth,
                                                          double* Rrow)
 {
@@ -292,13 +294,13 @@ __host__ __device__ __forceinline__ bool kabsch_rotation(const double* mom, cons
     const double dH = det3(Ht);
     const bool well = nh > 1e-14 * pq && dH > 0.0 && dH * dH > 1e-12 * nh * nh * nh;
     bool fast = false;
-    if (well && Rprev && (prev_orth || rot_orthogonal(Rprev))) {
+    if (kStep != kAfterRefine && well && Rprev && (prev_orth || rot_orthogonal(Rprev))) {
         const double Q0[3][3] = {{Rprev[0], Rprev[1], Rprev[2]}, {Rprev[3], Rprev[4], Rprev[5]},
                                  {Rprev[6], Rprev[7], Rprev[8]}};
         fast = polar_refine(Ht, rough_rsqrt(nh), Q0, R);
     }
     if (!fast) {
-        if (kRefineOnly) return false;
+        if (kStep == kRefine) return false;
         if (!(well && polar3(Ht, R))) {
             const double floor_ = 1e-13 * sqrt(pq);
             double U[3][3], sig[3], V[3][3];
@@ -331,7 +333,7 @@ __host__ __device__ __forceinline__ bool kabsch(const double* mom, const double 
                                                 const double* Rprev, bool prev_orth)
 {
     double R[9];
-    if (!kabsch_rotation<false>(mom, Rprev, prev_orth, R)) return false;
+    if (!kabsch_rotation<kSolveAll>(mom, Rprev, prev_orth, R)) return false;
     for (int i = 0; i < 9; ++i) Rt[i] = R[i];
     kabsch_translation(mom, c, R, Rt + 9);
     return true;
