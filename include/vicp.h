@@ -291,7 +291,9 @@ int vicp_register_batched(const vicp_grid* g, const float* px, const float* py, 
  * per iteration, or the latter after the one launch handed over (a query
  * without a finite distance, or blocks that did not meet).  NONE before the
  * first, and after one without iterations or source points.  Every form gives
- * the same results. */
+ * the same correspondences and counts, and the same poses to the last bit,
+ * except where 64 queries' global searches meet more than 2^18 points in
+ * crowded voxels: the moment sums then come in another order. */
 #define VICP_FORM_NONE 0
 #define VICP_FORM_LOOP 1
 #define VICP_FORM_STEPS 2

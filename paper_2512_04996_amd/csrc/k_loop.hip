@@ -130,8 +130,15 @@ __device__ __forceinline__ T* uniform_ptr(T* p)
 
 // The block's global searches, shared out over its waves.  Out of line: most
 // iterations have none, and inlined its registers would be the search's too.
-__device__ __attribute__((noinline)) bool block_misses(const PairDev* P, const uint32_t* off, const uint8_t* pyr,
-                                                       const float4* qs4, MissSlot* slots, int n)
+// kRest: those that the first pass left, among crowded voxels, in a function of
+// their own, as their registers and a call from within cost the ordinary ones
+// more (a 2,048-point sphere, 20 steps: 295 us, 314 with a call from within).
+// Returns kAllFound when every search of the wave has a finite distance, and
+// kSomeLeft when some were left.
+constexpr int kAllFound = 1, kSomeLeft = 2;
+template <bool kRest>
+__device__ __forceinline__ int wave_misses(const PairDev* P, const uint32_t* off, const uint8_t* pyr, const float4* qs4,
+                                           MissSlot* slots, int n)
 {
     P = uniform_ptr(P);
     off = uniform_ptr(off);
@@ -139,11 +146,26 @@ __device__ __attribute__((noinline)) bool block_misses(const PairDev* P, const u
     qs4 = uniform_ptr(qs4);
     n = __builtin_amdgcn_readfirstlane(n);
     const int lane = threadIdx.x & (kWave - 1);
-    bool all = true;
+    int got = kAllFound;
     for (int e = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); e < n; e += kLoopWaves) {
-        float rd = 0.0f, rx = 0.0f, ry = 0.0f, rz = 0.0f;
-        uint32_t rj = 0u;
-        all &= tree_nearest<kCubeMin>(*P, off, pyr, qs4, slots[e].s[0], slots[e].s[1], slots[e].s[2], rd, rj, rx, ry, rz);
+        float rd = INFINITY, rx = 0.0f, ry = 0.0f, rz = 0.0f;
+        uint32_t rj = 0xFFFFFFFFu, budget = 1u;
+        if (kRest) {
+            // left: the negative of the best found, from which this goes on
+            const uint32_t d = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(slots[e].d));
+            if (!(d >> 31)) continue;
+            rd = __uint_as_float(d & 0x7FFFFFFFu);
+            rx = slots[e].x, ry = slots[e].y, rz = slots[e].z;
+            rj = slots[e].j;
+        }
+        const bool ok = tree_nearest<kCubeMin, kRest ? kCrowdScan : kCrowdLeave, kRest>(
+            *P, off, pyr, qs4, slots[e].s[0], slots[e].s[1], slots[e].s[2], rd, rj, rx, ry, rz, budget);
+        if (!kRest && budget == 0u) {   // uniform
+            got |= kSomeLeft;
+            rd = __uint_as_float(__float_as_uint(rd) | 0x80000000u);
+        } else if (!ok) {
+            got &= ~kAllFound;
+        }
         if (lane == 0) {
             slots[e].d = rd;
             slots[e].x = rx;
@@ -152,7 +174,17 @@ __device__ __attribute__((noinline)) bool block_misses(const PairDev* P, const u
             slots[e].j = rj;
         }
     }
-    return all;
+    return got;
+}
+__device__ __attribute__((noinline)) int block_misses(const PairDev* P, const uint32_t* off, const uint8_t* pyr,
+                                                      const float4* qs4, MissSlot* slots, int n)
+{
+    return wave_misses<false>(P, off, pyr, qs4, slots, n);
+}
+__device__ __attribute__((noinline)) int block_crowd_misses(const PairDev* P, const uint32_t* off, const uint8_t* pyr,
+                                                            const float4* qs4, MissSlot* slots, int n)
+{
+    return wave_misses<true>(P, off, pyr, qs4, slots, n);
 }
 
 // crowd_scan, out of line: most searches have no crowded voxel, and inlined its
@@ -344,8 +376,11 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
                 __syncthreads();
                 const int nmiss = sh.misses;
                 if (pass == 1 || nmiss == 0) break;   // uniform over the block
-                // false: no finite distance, the other form resolves it
-                if (!block_misses(&P, B->off, B->pyr, B->qs4, slots, nmiss) && lane == 0) sh.stop = 1;
+                int got = __builtin_amdgcn_readfirstlane(block_misses(&P, B->off, B->pyr, B->qs4, slots, nmiss));
+                if (got & kSomeLeft)
+                    got &= __builtin_amdgcn_readfirstlane(block_crowd_misses(&P, B->off, B->pyr, B->qs4, slots, nmiss));
+                // no finite distance: the other form resolves it
+                if (!(got & kAllFound) && lane == 0) sh.stop = 1;
                 __syncthreads();
                 if (miss) {
                     bd = slots[place].d;

@@ -24,8 +24,9 @@
 //
 // Global search (empty undilated voxel or outside the grid): the wave
 // resolves the query itself by an exact search of the occupancy pyramid.
-// Exhaustive search (queries without a finite distance): the query is appended to a per-pair list and a brute force over all targets
-// resolves it; partial minima from target tiles merge through a 64-bit
+// Exhaustive search (queries without a finite distance, or behind the budget of
+// a wave among crowded voxels): the query is appended to a per-pair list and a
+// brute force over all targets resolves it; partial minima from target tiles merge through a 64-bit
 // atomic minimum of (distance bits << 32 | index), which is order-free, so
 // the result is deterministic.
 #include <math.h>
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
                                                   unsigned long long* __restrict__ fb_key,
                                                   unsigned long long* __restrict__ ctr, double* __restrict__ part,
                                                   const uint32_t* __restrict__ dcnt, uint32_t cap,
-                                                  int64_t one_m, int early)
+                                                  int64_t one_m, int early, uint32_t most)
 {
     static_assert(LPQ == 1 || LPQ == 2 || LPQ == 4 || LPQ == 8, "lanes per query");
     constexpr bool kReload = kMode == 1;
@@ -230,15 +231,17 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
     }
     // Registration: the wave resolves its global searches itself, one query at
     // a time, by the exact tree search over the segments (qsg, whichever layout
-    // the local search reads); those without a finite distance are appended to
-    // the pair's list for the exhaustive search, one append per wave, each query
-    // at its rank among the wave's unresolved ones.  Every global search is
+    // the local search reads); those without a finite distance, and those behind
+    // the wave's budget of crowded voxels' points, are appended to the pair's
+    // list for the exhaustive search, one append per wave, each query at its rank
+    // among the wave's unresolved ones.  Every global search is
     // counted in fb_miss.
     bool treed = false;
     unsigned long long left = mmask;
     if (mmask) {
         unsigned long long pend = mmask;
         left = 0ull;
+        uint32_t budget = S.misses > kManyMisses ? kRareBudget : most;
         while (pend) {   // uniform over the wave
             const int L = __ffsll((long long)pend) - 1;
             pend &= pend - 1ull;
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
             const float lx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sx), L));
             const float ly = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sy), L));
             const float lz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sz), L));
-            if (tree_nearest<kCubeMin>(P, off, pyr, qsg, lx, ly, lz, rd, rj, rx, ry, rz)) {
+            if (tree_nearest<kCubeMin, kCrowdBudget>(P, off, pyr, qsg, lx, ly, lz, rd, rj, rx, ry, rz, budget)) {
                 if (lane == L) {
                     treed = true;
                     bd = rd;
@@ -258,6 +261,10 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
                 }
             } else {
                 left |= 1ull << L;
+                if (budget == 0u) {   // the others lie in the same crowd
+                    left |= pend;
+                    pend = 0ull;
+                }
             }
         }
         const int leader = __ffsll((long long)mmask) - 1;
@@ -506,9 +513,9 @@ __global__ __launch_bounds__(kGlThreads) void k_nns_global(
             transform(st[job.pair].Rtf, px[t], py[t], pz[t], s[0], s[1], s[2]);
             const auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
             float rd, rx, ry, rz;
-            uint32_t rj;
-            if (!tree_nearest<kCubeMinNN>(P, off, pyr, qs4, uniform(s[0]), uniform(s[1]), uniform(s[2]), rd, rj, rx, ry,
-                                          rz)) {
+            uint32_t rj, budget;
+            if (!tree_nearest<kCubeMinNN, kCrowdScan>(P, off, pyr, qs4, uniform(s[0]), uniform(s[1]), uniform(s[2]), rd, rj, rx, ry,
+                                                 rz, budget)) {
                 rd = INFINITY;
                 rj = 0u;
             }
@@ -528,7 +535,7 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
                       const uint2* dir, const uint32_t* off, const uint8_t* pyr, const float4* qs4, const float4* qsg,
                       int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list, unsigned long long* fb_key, unsigned long long* ctr,
                       double* part, const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m,
-                      int early, hipStream_t s)
+                      int early, uint32_t budget, hipStream_t s)
 {
     if (njobs <= 0) return;
     const bool one = one_m >= 0;
@@ -539,11 +546,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
     if (one)                                                                                                       \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m, early);                                                                                  \
+                     cap, one_m, early, budget);                                                            \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, true, false, 1, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m, early)
+                     cap, one_m, early, budget)
 #define VICP_NNS_RL(BS, SORTED)                                     \
     switch (lpq) {                                                  \
     case 1: VICP_NNS_R(BS, 1, SORTED); break;                       \
@@ -571,11 +578,11 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
     if (one && !DIRECT)                                                                                            \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, true>, dim3(njobs), dim3(BS), s, pd, jobs, px, py,  \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m, early);                                                                                  \
+                     cap, one_m, early, budget);                                                            \
     else                                                                                                           \
         launch_timed(k_nns_local<BS, L, SORTED, MOM, DIRECT, 0, false>, dim3(njobs), dim3(BS), s, pd, jobs, px, py, \
                      pz, ps4, st, dir, off, pyr, qs4, qsg, nn_idx, nn_d2, fb_count, fb_miss, fb_list, fb_key, ctr, part, dcnt,    \
-                     cap, one_m, early)
+                     cap, one_m, early, budget)
 #define VICP_NNS_L(BS, SORTED, MOM, DIRECT)                  \
     switch (lpq) {                                           \
     case 2: VICP_NNS(BS, 2, SORTED, MOM, DIRECT); break;     \

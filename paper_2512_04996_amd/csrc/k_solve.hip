@@ -196,6 +196,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(
     S.iters = k + 1;
     if (early_stop && k >= 1 && fabs(rmse - prev) < eps) S.done = 1;
     S.prev_rmse = rmse;
+    S.misses = nmiss;
 }
 
 // Initial state: pose rounded to float32 for the search; pairs with no

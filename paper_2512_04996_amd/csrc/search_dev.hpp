@@ -190,7 +190,10 @@ __device__ __forceinline__ void consider(const float4& q, float sx, float sy, fl
 // only while a target outside the node could still win; a far query descends
 // from the top.  Level-1 cells (bricks of 64 voxels) are taken kN at a time.
 // Voxels are read as rows along x, whose points are consecutive: two offsets
-// give a whole row's.
+// give a whole row's.  Where a lane would scan more than kSerialPoints of them
+// (crowded voxels), the first cube is dropped for the bricks, and a brick's
+// voxels are taken nearest first, each scanned by the whole wave, until none
+// left can hold a nearer target.
 //
 // Cells, and the grid box, are widened by a margin for the float32 rounding
 // of the voxel assignment (floor((q - o) * inv)), so a target assigned to a
@@ -198,8 +201,9 @@ __device__ __forceinline__ void consider(const float4& q, float sx, float sy, fl
 // by a factor 1 / (1 - 1e-4), far above the rounding of the float32
 // distance, so a dropped target can neither win nor tie.  All 64 lanes call
 // it with the same point; every lane gets the result.  False when the query
-// is not finite or no finite distance was found: it then goes to the
-// exhaustive search.
+// is not finite or no finite distance was found, and with kCrowdBudget also once
+// the budget of crowded voxels' points is used up (budget 0): it then goes to
+// the exhaustive search.
 //
 // What bounds it: the latency of its dependent loads (flags, offsets,
 // points).  Voxel cubes growing around the query, its former form, read
@@ -209,9 +213,13 @@ __device__ __forceinline__ void consider(const float4& q, float sx, float sy, fl
 // 88.3 ms before, 28.7 ms; the loss on 16 x 40k pairs (3.5% misses): 473 and
 // 393 us; a 2k sphere with 2% misses, 20 iterations: 568 and 479 us.  Reading
 // directory entries voxel by voxel instead of offsets row by row: 52.9 ms on
-// the first, 466 and 578 us on the others.
+// the first, 466 and 578 us on the others.  Crowded voxels (a room of 200,000
+// points on a 16^3 grid) scanned row by row, a 9^3 cube first: 10 steps with 860
+// misses inside the grid took 8.8 ms, nearest voxel first 2.2 (cubes with a limit
+// and the exhaustive search: 3.9); with 9,000 queries in overflowed blocks of
+// the direct layout 20 to 30 ms, now 4.3 (9.3).
 constexpr float kBoundSlack = 1.0f - 1e-4f;
-constexpr uint32_t kSerialPoints = 96;   // points a lane scans alone; above that the wave scans row by row
+constexpr uint32_t kSerialPoints = 96;   // points a lane scans alone; above that the wave scans voxel by voxel
 constexpr int kN = 2;                    // rows per lane and round: of a cube, or of as many bricks
 constexpr int kLoads = 4;                // point loads in flight per lane
 constexpr int kCubeMin = 2;              // the first cube's smallest radius (registration): 5^3 voxels
@@ -253,20 +261,109 @@ __device__ __forceinline__ float row_bound(const TreeBox& b, int x0, int x1, int
     return lb;
 }
 
-template <int kFirst>
-__device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* __restrict__ off,
-                                             const uint8_t* __restrict__ pyr, const float4* __restrict__ qs4, float sx,
-                                             float sy, float sz, float& rd, uint32_t& rj, float& rx, float& ry,
-                                             float& rz)
+__device__ __forceinline__ TreeBox tree_box(const PairDev& P, float sx, float sy, float sz)
 {
-    if (!(isfinite(sx) && isfinite(sy) && isfinite(sz))) return false;   // left to the exhaustive search
-    const int lane = threadIdx.x & (kWave - 1);
-    const int lx = lane & 3, ly = (lane >> 2) & 3, lz = lane >> 4;
     TreeBox b;
     b.s[0] = sx, b.s[1] = sy, b.s[2] = sz;
     b.o[0] = P.ox, b.o[1] = P.oy, b.o[2] = P.oz;
     b.D[0] = P.Dx, b.D[1] = P.Dy, b.D[2] = P.Dz;
     b.vox = 1.0f / P.inv;
+    // 1e-5 of the coordinates' magnitude and 1e-3 of a voxel: far above the
+    // float32 rounding of the assignment and of the bounds' arithmetic
+#pragma unroll
+    for (int a = 0; a < 3; ++a) b.mg[a] = 1e-5f * (fabsf(b.o[a]) + ((float)b.D[a] + 1.0f) * b.vox) + 1e-3f * b.vox;
+    return b;
+}
+
+// The points of the voxels [x0, x1) of row (y, z) as (first slot in qs4,
+// number): consecutive voxels' segments follow each other, and every voxel
+// before g has two header words in off[g].
+__device__ __forceinline__ uint2 row_run(const PairDev& P, const TreeBox& b, const uint32_t* __restrict__ off, int x0,
+                                         int x1, int y, int z)
+{
+    const int64_t g0 = P.v_base + x0 + (int64_t)b.D[0] * (y + (int64_t)b.D[1] * z), g1 = g0 + (x1 - x0);
+    const uint32_t a0 = off[g0], a1 = off[g1];
+    return make_uint2(a0 - 2u * (uint32_t)g0, a1 - a0 - 2u * (uint32_t)(x1 - x0));
+}
+
+// A search's best so far: the lane's own, and the wave's least distance.
+struct TreeBest {
+    float d, x, y, z, wave;
+    uint32_t j;
+    __device__ __forceinline__ void take(const float4& q, float sx, float sy, float sz)
+    {
+        const float e = dist2(sx, sy, sz, q.x, q.y, q.z);
+        const uint32_t i = __float_as_uint(q.w);
+        const bool better = e < d || (e == d && i < j);
+        d = better ? e : d;
+        j = better ? i : j;
+        x = better ? q.x : x;
+        y = better ? q.y : y;
+        z = better ? q.z : z;
+    }
+    // distances are >= 0: their bits order as the values do
+    __device__ __forceinline__ void combine() { wave = __uint_as_float(wave_min_dpp(__float_as_uint(d))); }
+};
+
+// The voxels of a brick (of which (x0, y0, z0) is the first) nearest first, each
+// scanned by the whole wave, with its row where the row is one round of loads.
+// False when the budget is used up (kGiveUp).
+template <bool kGiveUp>
+__device__ __forceinline__ bool crowd_brick(const PairDev& P, const TreeBox& b, const uint32_t* __restrict__ off,
+                                            const float4* __restrict__ qs4, int x0, int y0, int z0, TreeBest& t,
+                                            uint32_t& budget)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int x = x0 + (lane & 3), y = y0 + ((lane >> 2) & 3), z = z0 + (lane >> 4);
+    uint2 ev = make_uint2(0u, 0u);
+    if (x < b.D[0] && y < b.D[1] && z < b.D[2]) ev = row_run(P, b, off, x, x + 1, y, z);
+    const float lb = row_bound(b, x, x + 1, y, z);
+    // the row's run, in each of its four lanes
+    uint2 rw = make_uint2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)ev.x, 0x00, 0xF, 0xF, true), ev.y);   // quad_perm 0,0,0,0
+    rw.y += xor_lanes(rw.y, 1);
+    rw.y += xor_lanes(rw.y, 2);
+    if (rw.y <= kLoads * kWave) ev = rw;
+    unsigned long long left = __ballot(ev.y > 0u);
+    while (left) {   // uniform
+        const bool mine = (left >> lane) & 1ull;
+        const float m = __uint_as_float(wave_min_dpp(mine ? __float_as_uint(lb) : 0xFFFFFFFFu));
+        if (m * kBoundSlack > t.wave) break;
+        const int L = __ffsll((long long)__ballot(mine && lb == m)) - 1;
+        const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)ev.x, L);
+        const uint32_t cn = (uint32_t)__builtin_amdgcn_readlane((int)ev.y, L);
+        left &= ~((uint32_t)__builtin_amdgcn_readlane((int)rw.y, L) <= kLoads * kWave ? 0xFull << (L & ~3) : 1ull << L);
+        if (kGiveUp) {
+            budget -= min(cn, budget);
+            if (budget == 0u) return false;
+        }
+        for (uint32_t k = lane; k < cn; k += kLoads * kWave) {
+            float4 q[kLoads];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) q[i] = qs4[st + min(k + (uint32_t)(i * kWave), cn - 1u)];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) t.take(q[i], b.s[0], b.s[1], b.s[2]);
+        }
+        t.combine();
+    }
+    return true;
+}
+
+// What a search does among crowded voxels: scan them, scan them within the
+// budget, or leave (budget 0, the results the best found so far).
+enum Crowd { kCrowdScan, kCrowdBudget, kCrowdLeave };
+
+// kFirst: the first cube's smallest radius.  kSeed: the results hold a target
+// already found (or no finite distance), from which the search starts.
+template <int kFirst, Crowd kCrowd, bool kSeed = false>
+__device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* __restrict__ off,
+                                             const uint8_t* __restrict__ pyr, const float4* __restrict__ qs4, float sx,
+                                             float sy, float sz, float& rd, uint32_t& rj, float& rx, float& ry,
+                                             float& rz, uint32_t& budget)
+{
+    if (!(isfinite(sx) && isfinite(sy) && isfinite(sz))) return false;   // left to the exhaustive search
+    const int lane = threadIdx.x & (kWave - 1);
+    const int lx = lane & 3, ly = (lane >> 2) & 3, lz = lane >> 4;
+    const TreeBox b = tree_box(P, sx, sy, sz);
     int v0[3];
     float d2box[3];
 #pragma unroll
@@ -274,9 +371,6 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
         const float f = (b.s[a] - b.o[a]) * P.inv;
         const int c = f < 0.0f ? 0 : (f >= (float)(b.D[a] - 1) ? b.D[a] - 1 : (int)floorf(f));
         v0[a] = __builtin_amdgcn_readfirstlane(c);
-        // 1e-5 of the coordinates' magnitude and 1e-3 of a voxel: far above
-        // the float32 rounding of the assignment and of this arithmetic
-        b.mg[a] = 1e-5f * (fabsf(b.o[a]) + ((float)b.D[a] + 1.0f) * b.vox) + 1e-3f * b.vox;
         const float lo = b.o[a] - b.mg[a], hi = b.o[a] + (float)b.D[a] * b.vox + b.mg[a];
         const float g = b.s[a] < lo ? lo - b.s[a] : (b.s[a] > hi ? b.s[a] - hi : 0.0f);
         d2box[a] = g * g;
@@ -300,19 +394,9 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
         }
         return out;
     };
-    // each lane keeps its own best; `best` is the wave's
-    float bd = INFINITY, bx = 0.0f, by = 0.0f, bz = 0.0f, best = INFINITY;
-    uint32_t bj = 0xFFFFFFFFu;
-    auto take = [&](const float4& q) {
-        const float d = dist2(sx, sy, sz, q.x, q.y, q.z);
-        const uint32_t j = __float_as_uint(q.w);
-        const bool better = d < bd || (d == bd && j < bj);
-        bd = better ? d : bd;
-        bj = better ? j : bj;
-        bx = better ? q.x : bx;
-        by = better ? q.y : by;
-        bz = better ? q.z : bz;
-    };
+    TreeBest t = {INFINITY, 0.0f, 0.0f, 0.0f, INFINITY, 0xFFFFFFFFu};
+    if (kSeed && lane == 0) t = TreeBest{rd, rx, ry, rz, rd, rj};
+    if (kSeed) t.wave = rd;
     // the first cube reaches one voxel past the dilation: a global search's
     // voxel has no occupied voxel within L1 distance L
     const int top = P.t_top;
@@ -321,14 +405,6 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
     static_assert((2 * kCubeMax + 1) * (2 * kCubeMax + 1) <= kN * kWave, "a cube's rows fit one round");
     const float reach = (float)R * b.vox;
     bool cube = top > 0 && d2box[0] + d2box[1] + d2box[2] <= reach * reach;
-    // the points of the voxels [x0, x1) of row (y, z): consecutive voxels'
-    // segments follow each other, and every voxel before g has two header
-    // words in off[g]
-    auto run = [&](int x0, int x1, int y, int z) {
-        const int64_t g0 = P.v_base + x0 + (int64_t)b.D[0] * (y + (int64_t)b.D[1] * z), g1 = g0 + (x1 - x0);
-        const uint32_t a0 = off[g0], a1 = off[g1];
-        return make_uint2(a0 - 2u * (uint32_t)g0, a1 - a0 - 2u * (uint32_t)(x1 - x0));
-    };
     const int ry_ = (lane >> 2) & 3, rz_ = lane >> 4;   // the lane's row in a brick
     // children of level l of the node (nx, ny, nz); `rem` are those still to
     // be looked at, kept per level in lane l of stk while a child's own
@@ -343,6 +419,7 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
     // their points
     while (true) {
         uint2 e[kN];   // runs of the lane: first point in qs4, points
+        uint32_t bricks = 0u;            // the round's bricks: 1 + its place in the node, a byte each
         if (cube) {
 #pragma unroll
             for (int u = 0; u < kN; ++u) {
@@ -352,7 +429,7 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
                 // a voxel past 2^31 wraps to a negative index
                 const int vy = (int)((uint32_t)v0[1] + (uint32_t)(y - R)), vz = (int)((uint32_t)v0[2] + (uint32_t)(z - R));
                 const int x0 = max(v0[0] - R, 0), x1 = (int)min((uint32_t)v0[0] + R + 1u, (uint32_t)b.D[0]);
-                if (it < w * w && vy >= 0 && vz >= 0 && vy < b.D[1] && vz < b.D[2]) e[u] = run(x0, x1, vy, vz);
+                if (it < w * w && vy >= 0 && vz >= 0 && vy < b.D[1] && vz < b.D[2]) e[u] = row_run(P, b, off, x0, x1, vy, vz);
             }
         } else {
             const int cx = 4 * nx + lx, cy = 4 * ny + ly, cz = 4 * nz + lz;
@@ -369,7 +446,7 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
             }
             float lb = (rem >> lane) & 1ull ? cell_bound(b, l, cx, cy, cz) : INFINITY;
             float m = __uint_as_float(wave_min_dpp(__float_as_uint(lb)));
-            if (!rem || m * kBoundSlack > best) {   // nothing left here
+            if (!rem || m * kBoundSlack > t.wave) {   // nothing left here
                 if (top == 0) break;
                 if (l < up) {   // back to the node above
                     ++l;
@@ -385,7 +462,7 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
                 const int hi[3] = {(int)min((uint32_t)(nx + 1) << sh, (uint32_t)b.D[0]),
                                    (int)min((uint32_t)(ny + 1) << sh, (uint32_t)b.D[1]),
                                    (int)min((uint32_t)(nz + 1) << sh, (uint32_t)b.D[2])};
-                if (outside(lo, hi) * kBoundSlack > best) break;
+                if (outside(lo, hi) * kBoundSlack > t.wave) break;
                 came = (nx & 3) | ((ny & 3) << 2) | ((nz & 3) << 4);
                 nx >>= 2, ny >>= 2, nz >>= 2;
                 up = ++l;
@@ -408,20 +485,21 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
             for (int u = 0; u < kN; ++u) {
                 e[u] = make_uint2(0u, 0u);
                 if (u > 0) m = __uint_as_float(wave_min_dpp(__float_as_uint(lb)));
-                if (!rem || m * kBoundSlack > best || (u > 0 && best == INFINITY)) continue;   // uniform
+                if (!rem || m * kBoundSlack > t.wave || (u > 0 && t.wave == INFINITY)) continue;   // uniform
                 const int pick = __ffsll((long long)__ballot(((rem >> lane) & 1ull) && lb == m)) - 1;
                 rem &= ~(1ull << pick);
                 lb = lane == pick ? INFINITY : lb;
+                bricks |= (uint32_t)(pick + 1) << (8 * u);
                 const int x0 = 4 * (4 * nx + (pick & 3)), vy = 4 * (4 * ny + ((pick >> 2) & 3)) + ry_,
                           vz = 4 * (4 * nz + (pick >> 4)) + rz_;
                 const int x1 = (int)min((uint32_t)x0 + 4u, (uint32_t)b.D[0]);
-                if (vy < b.D[1] && vz < b.D[2] && !(row_bound(b, x0, x1, vy, vz) * kBoundSlack > best))
-                    e[u] = run(x0, x1, vy, vz);
+                if (vy < b.D[1] && vz < b.D[2] && !(row_bound(b, x0, x1, vy, vz) * kBoundSlack > t.wave))
+                    e[u] = row_run(P, b, off, x0, x1, vy, vz);
             }
         }
         // the lane's share of its runs' points (every 4th of a brick's row) as
         // one flat run, kLoads in flight (a lane past its last point repeats
-        // it); where a lane would scan many, all lanes scan one run at a time
+        // it); where a lane would scan many, voxel by voxel
         const uint32_t first = cube ? 0u : (uint32_t)(lane & 3), sh = cube ? 0u : 2u;
         uint32_t own[kN], total = 0u;
 #pragma unroll
@@ -433,8 +511,8 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
             for (uint32_t t0 = 0; t0 < total; t0 += kLoads) {
                 float4 q[kLoads];
 #pragma unroll
-                for (int t = 0; t < kLoads; ++t) {
-                    uint32_t f = min(t0 + (uint32_t)t, total - 1u), slot = 0u;
+                for (int i = 0; i < kLoads; ++i) {
+                    uint32_t f = min(t0 + (uint32_t)i, total - 1u), slot = 0u;
                     bool found = false;
 #pragma unroll
                     for (int u = 0; u < kN; ++u) {
@@ -443,52 +521,43 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
                         found |= here;
                         f -= own[u];
                     }
-                    q[t] = qs4[slot];
+                    q[i] = qs4[slot];
                 }
 #pragma unroll
-                for (int t = 0; t < kLoads; ++t) take(q[t]);
+                for (int i = 0; i < kLoads; ++i) t.take(q[i], sx, sy, sz);
             }
+        } else if (kCrowd == kCrowdLeave) {
+            budget = 0u;
+            break;
+        } else if (cube) {
+            cube = false;
+            continue;
         } else {
-#pragma unroll 1
-            for (int u = 0; u < kN; ++u) {
-                uint2 eu = e[0];
-#pragma unroll
-                for (int v = 1; v < kN; ++v) eu = u == v ? e[v] : eu;
-                unsigned long long left = __ballot(eu.y > 0u && first == 0u);
-                while (left) {
-                    const int L = __ffsll((long long)left) - 1;
-                    left &= left - 1ull;
-                    const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)eu.x, L);
-                    const uint32_t cn = (uint32_t)__builtin_amdgcn_readlane((int)eu.y, L);
-                    for (uint32_t k = lane; k < cn; k += kLoads * kWave) {
-                        float4 q[kLoads];
-#pragma unroll
-                        for (int t = 0; t < kLoads; ++t) q[t] = qs4[st + min(k + (uint32_t)(t * kWave), cn - 1u)];
-#pragma unroll
-                        for (int t = 0; t < kLoads; ++t) take(q[t]);
-                    }
-                }
+            for (; bricks; bricks >>= 8) {   // uniform
+                const int pick = (int)(bricks & 0xFFu) - 1;
+                const int x0 = 4 * (4 * nx + (pick & 3)), y0 = 4 * (4 * ny + ((pick >> 2) & 3)), z0 = 4 * (4 * nz + (pick >> 4));
+                if (!crowd_brick<kCrowd == kCrowdBudget>(P, b, off, qs4, x0, y0, z0, t, budget)) return false;
             }
         }
-        best = __uint_as_float(wave_min_dpp(__float_as_uint(bd)));   // >= 0: bits order as values
+        t.combine();
         if (cube) {
             cube = false;
             const int lo[3] = {max(v0[0] - R, 0), max(v0[1] - R, 0), max(v0[2] - R, 0)};
             const int hi[3] = {(int)min((uint32_t)v0[0] + R + 1u, (uint32_t)b.D[0]),
                                (int)min((uint32_t)v0[1] + R + 1u, (uint32_t)b.D[1]),
                                (int)min((uint32_t)v0[2] + R + 1u, (uint32_t)b.D[2])};
-            if (outside(lo, hi) * kBoundSlack > best) break;
+            if (outside(lo, hi) * kBoundSlack > t.wave) break;
         }
     }
-    if (!(best < INFINITY)) return false;
+    if (!(t.wave < INFINITY)) return false;
     // the lowest index among the lanes at the best distance
-    const uint32_t j = wave_min_dpp(bd == best ? bj : 0xFFFFFFFFu);
-    const int owner = __ffsll((long long)__ballot(bd == best && bj == j)) - 1;
-    rd = best;
+    const uint32_t j = wave_min_dpp(t.d == t.wave ? t.j : 0xFFFFFFFFu);
+    const int owner = __ffsll((long long)__ballot(t.d == t.wave && t.j == j)) - 1;
+    rd = t.wave;
     rj = j;
-    rx = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(bx), owner));
-    ry = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(by), owner));
-    rz = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(bz), owner));
+    rx = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(t.x), owner));
+    ry = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(t.y), owner));
+    rz = __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(t.z), owner));
     return true;
 }
 

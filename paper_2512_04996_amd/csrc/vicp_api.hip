@@ -627,6 +627,7 @@ struct vicp_grid {
     uint32_t loop_tag = 0;
     LoopJob* loop_jobs = nullptr;   // a batch's blocks, for loop_lpq lanes per query
     int loop_lpq = 0, loop_blocks = 0;
+    uint32_t step_budget = kRareBudget;   // of the launch-per-step search's waves (kStepBudget)
     int32_t last_form = VICP_FORM_NONE;   // how the last registration ran
 
     // Captured work: the registration (plan + iterations).
@@ -1005,7 +1006,8 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
         launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, g->sort_src, true, px, py,
                          pz, g->ps4, g->st, g->dir, g->off, g->pyr, direct ? g->dblk : g->qs4, g->qs4, nn_idx, nn_d2,
                          g->fb_count, g->fb_count + g->B, g->fb_list, g->fb_key, g->ctr, g->npart,
-                         direct ? g->dcnt : nullptr, g->dcap, g->search_mode, g->B == 1 ? g->m[0] : -1, early, s);
+                         direct ? g->dcnt : nullptr, g->dcap, g->search_mode, g->B == 1 ? g->m[0] : -1, early,
+                         g->step_budget, s);
     }
     ProfScope ps("fallback", s, cap, true);
     return launch_fallback(g->d_pd, g->B, g->fb_grid, g->qx, g->qy, g->qz, px, py, pz, g->st, g->fb_count,
@@ -1028,7 +1030,7 @@ void queue_correspondences(vicp_grid* g, const float* px, const float* py, const
         ProfScope ps("nns_local", s, cap, true);
         launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, false, false, px, py, pz,
                          g->ps4, g->st, g->dir, g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, miss, nullptr,
-                         nullptr, g->ctr, nullptr, nullptr, 0u, 0, g->B == 1 ? g->m[0] : -1, 0, s);
+                         nullptr, g->ctr, nullptr, nullptr, 0u, 0, g->B == 1 ? g->m[0] : -1, 0, 0u, s);
     }
     ProfScope ps("nns_global", s, cap, true);
     launch_nns_global(g->d_pd, g->jobs_p[tab], g->B, g->njobs_p[tab], g->nns_block, g->nns_lpq, px, py, pz, g->st, g->off,
@@ -1855,6 +1857,7 @@ __global__ void k_noalloc_setup(NaSetup a, int32_t njobs, int32_t qpb, unsigned 
         S.degenerate = 0;
         S.status = 0;
         S.rot_ok = 0;
+        S.misses = 0;
         int32_t* cnt = reinterpret_cast<int32_t*>(base + kNaOffCnt);
         cnt[2] = 0;   // queries that needed a global search
     }
@@ -1908,7 +1911,7 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb, base);
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
                      g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, cnt + 2, nullptr, nullptr, mask, nullptr,
-                     nullptr, 0u, 0, m, 0, s);
+                     nullptr, 0u, 0, m, 0, 0u, s);
     launch_nns_global(pd, jobs, 1, (int)njobs, g->nns_block, g->nns_lpq, px, py, pz, st, g->off, g->pyr, g->qs4, mask,
                       cnt + 2, nn_idx, nn_d2, n_fallback, s);
     hipError_t e = hipGetLastError();
@@ -1990,12 +1993,12 @@ int loop_capacity(int dev, int lpq, bool sorted)
 // Blocks of pair p's U units when every block takes at most r of them.
 int32_t loop_pair_blocks(int64_t U, int64_t r) { return (int32_t)((U + r - 1) / r); }
 
-// The number of loop blocks for the grid's source and schedule, with a batch's
-// table on the device; 0 when the loop does not take it.
-int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
+// The loop's blocks for the grid's source and schedule, U the units of each
+// pair and r the most of them a block takes; 0 when the loop does not take it.
+int loop_fit(const vicp_grid* g, int capacity, std::vector<int64_t>& U, int64_t& r)
 {
     const int lpq = g->nns_lpq, B = g->B;
-    std::vector<int64_t> U(B);
+    U.resize(B);
     int64_t total = 0, most = 0;
     for (int p = 0; p < B; ++p) {
         U[p] = record_units(wave_records(g->m[p], lpq));
@@ -2006,7 +2009,7 @@ int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
     // the fewest units per block for which all blocks fit; with more than
     // kLoopRounds the launch-per-step form, which has more waves in flight, is
     // the faster
-    int64_t r = std::max<int64_t>(1, (total + capacity - 1) / capacity);
+    r = std::max<int64_t>(1, (total + capacity - 1) / capacity);
     auto blocks = [&](int64_t rr) {
         int64_t n = 0;
         for (int p = 0; p < B; ++p) n += loop_pair_blocks(U[p], rr);
@@ -2017,8 +2020,18 @@ int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
     if (nb > capacity || r > kLoopRounds) return 0;
     for (int p = 0; p < B; ++p)   // a pair on one block keeps its units' sums there
         if (U[p] > loop_alone_units() && loop_pair_blocks(U[p], r) == 1) return 0;
-    if (B == 1) return (int)nb;
-    if (g->loop_lpq == lpq && g->loop_blocks == (int)nb) return (int)nb;
+    return (int)nb;
+}
+
+// loop_fit, with a batch's table on the device.
+int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
+{
+    const int lpq = g->nns_lpq, B = g->B;
+    std::vector<int64_t> U;
+    int64_t r = 0;
+    const int nb = loop_fit(g, capacity, U, r);
+    if (nb == 0 || B == 1) return nb;
+    if (g->loop_lpq == lpq && g->loop_blocks == nb) return nb;
     // blocks b, b + 8, ... share an XCD: a pair's blocks go there together,
     // the largest pairs first, each to the XCD with the most room
     std::vector<int> order(B);
@@ -2048,8 +2061,21 @@ int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
     }
     upload(jobs.data(), sizeof(LoopJob) * jobs.size(), g->loop_jobs, s);
     g->loop_lpq = lpq;
-    g->loop_blocks = (int)nb;
-    return (int)nb;
+    g->loop_blocks = nb;
+    return nb;
+}
+
+// What the launch-per-step search may scan of crowded voxels, by whether the
+// loop could take the same registration.
+void set_step_budget(vicp_grid* g)
+{
+    std::vector<int64_t> U;
+    int64_t r = 0;
+    int dev = -1;
+    g->step_budget = kRareBudget;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices &&
+        loop_fit(g, loop_capacity(dev, g->nns_lpq, g->sort_src), U, r) == 0)
+        g->step_budget = kStepBudget;
 }
 
 // The loop's launch: K iterations from the state now in g->st on nloop blocks
@@ -2152,6 +2178,7 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
     float* out_d2 = o->nn_d2;
     constexpr const char* kTooMany = "too many pairs for the global search";
     if (!started) queue_start(g, Rt_io, px, py, pz, s);
+    set_step_budget(g);
     bool plan = g->sort_src && !started;
     vicp_grid::Captured& cg = g->reg;
     int dev = -1;
@@ -2778,6 +2805,7 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
                     g->nns_lpq = lpq;
                     g->sort_src = sorted != 0;
                     g->search_mode = mode;
+                    set_step_budget(g);
                     const int nloop = loop_lock.owns_lock() ? loop_plan(g, loop_capacity(dev, lpq, g->sort_src), s) : 0;
                     if (nloop > 0 && (bs != 128 || mode != 0)) continue;
                     float t;

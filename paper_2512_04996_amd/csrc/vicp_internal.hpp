@@ -188,6 +188,7 @@ struct PairState {
     int32_t degenerate;
     int32_t status;     // latched device faults (bit 0: non-finite source)
     int32_t rot_ok;     // Rt's rotation is a solve's result (orthogonal to rounding)
+    int32_t misses;     // global searches of the last step (launch-per-step form)
 };
 
 // Pair p's registration state at pose rt (float64, R row-major then t) for a
@@ -210,6 +211,7 @@ __device__ __forceinline__ void init_pair_state(PairState* __restrict__ st, int 
     S.degenerate = 0;
     S.status = 0;
     S.rot_ok = 0;   // a caller's rotation: the first solve checks it
+    S.misses = 0;
 }
 
 // The pose applied to a source point: s = R p + t (R row-major, then t).
@@ -531,7 +533,19 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
                       const PairState* st, const uint2* dir, const uint32_t* off, const uint8_t* pyr,
                       const float4* qs4, const float4* qsg, int32_t* nn_idx, float* nn_d2, int32_t* fb_count, int32_t* fb_miss, uint32_t* fb_list,
                       unsigned long long* fb_key, unsigned long long* ctr, double* part,
-                      const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m, int early, hipStream_t s);
+                      const uint32_t* dcnt, uint32_t cap, int mode, int64_t one_m, int early, uint32_t budget,
+                      hipStream_t s);
+// Among crowded voxels a wave of the registration search scans at most `budget`
+// points for its global searches; the rest of them go to the exhaustive search,
+// which has the whole device, while the wave resolves up to 64 one after the
+// other.  Sources that the resident loop never takes: kStepBudget (40 rounds of
+// loads).  200,000 points on a 16^3 grid, 180 queries far outside, 10 steps: 2.9
+// ms so (4 lanes), 6.2 all in place; but with 18,000 of them 33 against 8, so
+// after a step with more than kManyMisses, and for sources that the loop may
+// take too, whose sums must come in its order, kRareBudget (0.4 ms), which only
+// extremes reach.
+constexpr uint32_t kStepBudget = 10240, kRareBudget = 1u << 18;
+constexpr int32_t kManyMisses = 4096;
 // The search of every query over every target: `part` holds a word per source
 // point (of all pairs: `total`) and split of the targets.  The splits are
 // chosen so that the blocks' rounds on the device's compute units are full:
