@@ -474,10 +474,12 @@ __global__ __launch_bounds__(kFbThreads) void k_fallback(const PairDev* __restri
 // Block 0 also hands out the counts.
 constexpr int kGlThreads = 512, kGlBatch = 256;
 constexpr int kGlMaxBlocks = 768;
+template <bool kSorted>
 __global__ __launch_bounds__(kGlThreads) void k_nns_global(
     const PairDev* __restrict__ pd, const BlockJob* __restrict__ jobs, int npairs, int nrec, int waves, int lpq,
     const float* __restrict__ px, const float* __restrict__ py, const float* __restrict__ pz,
-    const PairState* __restrict__ st, const uint32_t* __restrict__ off, const uint8_t* __restrict__ pyr, const float4* __restrict__ qs4, const unsigned long long* __restrict__ mask,
+    const float4* __restrict__ ps4, const PairState* __restrict__ st, const uint32_t* __restrict__ off,
+    const uint8_t* __restrict__ pyr, const float4* __restrict__ qs4, const unsigned long long* __restrict__ mask,
     const int32_t* __restrict__ fb_miss, int32_t* __restrict__ nn_idx, float* __restrict__ nn_d2,
     int32_t* __restrict__ n_fallback)
 {
@@ -508,9 +510,11 @@ __global__ __launch_bounds__(kGlThreads) void k_nns_global(
             const int64_t job_at = rec / waves;
             const BlockJob job = jobs[job_at];
             const PairDev& P = pd[job.pair];
-            const int64_t t = P.p_base + job.start + ((rec - job_at * waves) * kWave + item % kWave) / lpq;
+            const int64_t at = P.p_base + job.start + ((rec - job_at * waves) * kWave + item % kWave) / lpq;
+            const float4 p = kSorted ? ps4[at] : make_float4(px[at], py[at], pz[at], 0.0f);
+            const int64_t t = kSorted ? P.p_base + __float_as_uint(p.w) : at;
             float s[3];
-            transform(st[job.pair].Rtf, px[t], py[t], pz[t], s[0], s[1], s[2]);
+            transform(st[job.pair].Rtf, p.x, p.y, p.z, s[0], s[1], s[2]);
             const auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
             float rd, rx, ry, rz;
             uint32_t rj, budget;
@@ -609,7 +613,9 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
         } else {
             VICP_NNS_BS(false, true, false)
         }
-    } else {   // correspondences: always in index order
+    } else if (sorted) {
+        VICP_NNS_BS(true, false, false)
+    } else {
         VICP_NNS_BS(false, false, false)
     }
 #undef VICP_NNS_BS
@@ -629,17 +635,17 @@ bool launch_fallback(const PairDev* pd, int npairs, int grid, const float* qx, c
     return true;
 }
 
-void launch_nns_global(const PairDev* pd, const BlockJob* jobs, int npairs, int njobs, int block, int lpq,
-                       const float* px, const float* py, const float* pz, const PairState* st, const uint32_t* off,
-                       const uint8_t* pyr, const float4* qs4, const unsigned long long* mask, const int32_t* fb_miss,
+void launch_nns_global(const PairDev* pd, const BlockJob* jobs, int npairs, int njobs, int block, int lpq, bool sorted,
+                       const float* px, const float* py, const float* pz, const float4* ps4, const PairState* st,
+                       const uint32_t* off, const uint8_t* pyr, const float4* qs4, const unsigned long long* mask, const int32_t* fb_miss,
                        int32_t* nn_idx, float* nn_d2, int32_t* n_fallback, hipStream_t s)
 {
     if (njobs <= 0) return;
     const int waves = block / kWave;
     const int64_t nrec = (int64_t)njobs * waves;
     const int nb = (int)std::min<int64_t>((nrec + kGlThreads / kWave - 1) / (kGlThreads / kWave), kGlMaxBlocks);
-    launch_timed(k_nns_global, dim3(nb), dim3(kGlThreads), s, pd, jobs, npairs, (int)nrec, waves, lpq, px, py, pz, st,
-                 off, pyr, qs4, mask, fb_miss, nn_idx, nn_d2, n_fallback);
+    launch_timed(sorted ? k_nns_global<true> : k_nns_global<false>, dim3(nb), dim3(kGlThreads), s, pd, jobs, npairs,
+                 (int)nrec, waves, lpq, px, py, pz, ps4, st, off, pyr, qs4, mask, fb_miss, nn_idx, nn_d2, n_fallback);
 }
 
 }  // namespace vicp

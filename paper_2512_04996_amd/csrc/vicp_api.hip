@@ -1015,25 +1015,40 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
                            g->nfjobs[tab][wpb_index(g->nns_block)], g->npart, g->ctr, g->fpart, g->fctr, s);
 }
 
+// Whether a single search buckets its source by target voxel first.  The five
+// launches of that cost about 20 us with 100,000 queries and 150 with 900,000,
+// more than they save where voxels hold few points (a room of 226,000: 35 us
+// against 103 with as many queries on a 64^3 grid, 95 against 243 with 900,000; at
+// 7 points a voxel 132 against 113), but not where a wave in index order waits for
+// the most crowded of its voxels: 576 against 280 us on a 16^3 grid (55 points a
+// voxel), 1460 against 748 on 8^3.  Below 50,000 queries, and below 1.5M points of
+// average voxels to scan, the two are within 5 us or bucketing is the slower (35
+// against 49 us with 40,000 queries at 10 points a voxel).
+bool bucket_single_search(const vicp_grid* g)
+{
+    const double mean = (double)g->n_total / (double)g->V_total;
+    return g->sort_src && mean >= 4.0 && g->m_total >= 50000 && mean * (double)g->m_total >= 1.5e6;
+}
+
 // The correspondences of every pair at the poses in g->st and (unless null)
-// each pair's count of global searches.  Over the source in index order,
-// whatever the schedule: bucketing it takes five launches, more than it saves
-// one search (a room of 226,000 points: 26 us against 57 with 200,000 queries,
-// 47 against 238 with a million in random order; a surface whose global
-// searches crowd: 25 against 43 with 2,000, 320 against 294 with a million).
+// each pair's count of global searches, over the source in index order or
+// bucketed (bucket_single_search).
 void queue_correspondences(vicp_grid* g, const float* px, const float* py, const float* pz, int32_t* nn_idx, float* nn_d2,
                            int32_t* n_fallback, hipStream_t s, bool cap)
 {
     const int tab = table_of(g->nns_block / g->nns_lpq);
     int32_t* miss = n_fallback ? g->fb_count + g->B : nullptr;
+    const bool sorted = bucket_single_search(g);
+    if (sorted) queue_plan(g, px, py, pz, s, cap);
     {
         ProfScope ps("nns_local", s, cap, true);
-        launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, false, false, px, py, pz,
+        launch_nns_local(g->d_pd, g->jobs_p[tab], g->njobs_p[tab], g->nns_block, g->nns_lpq, sorted, false, px, py, pz,
                          g->ps4, g->st, g->dir, g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, miss, nullptr,
                          nullptr, g->ctr, nullptr, nullptr, 0u, 0, g->B == 1 ? g->m[0] : -1, 0, 0u, s);
     }
     ProfScope ps("nns_global", s, cap, true);
-    launch_nns_global(g->d_pd, g->jobs_p[tab], g->B, g->njobs_p[tab], g->nns_block, g->nns_lpq, px, py, pz, g->st, g->off,
+    launch_nns_global(g->d_pd, g->jobs_p[tab], g->B, g->njobs_p[tab], g->nns_block, g->nns_lpq, sorted, px, py, pz,
+                      g->ps4, g->st, g->off,
                       g->pyr, g->qs4, g->ctr, miss, nn_idx, nn_d2, n_fallback, s);
 }
 
@@ -1912,7 +1927,8 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
                      g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, cnt + 2, nullptr, nullptr, mask, nullptr,
                      nullptr, 0u, 0, m, 0, 0u, s);
-    launch_nns_global(pd, jobs, 1, (int)njobs, g->nns_block, g->nns_lpq, px, py, pz, st, g->off, g->pyr, g->qs4, mask,
+    launch_nns_global(pd, jobs, 1, (int)njobs, g->nns_block, g->nns_lpq, false, px, py, pz, nullptr, st, g->off, g->pyr,
+                      g->qs4, mask,
                       cnt + 2, nn_idx, nn_d2, n_fallback, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(VICP_ERR_HIP, std::string("nns_noalloc: ") + hipGetErrorString(e));

@@ -597,9 +597,9 @@ bool launch_fallback(const PairDev* pd, int npairs, int grid, const float* qx, c
                      const uint32_t* fb_list, unsigned long long* fb_key, const FoldJob* fjobs, int nfjobs,
                      const double* part, const unsigned long long* ctr, double* fpart,
                      unsigned long long* fctr, hipStream_t s);
-void launch_nns_global(const PairDev* pd, const BlockJob* jobs, int npairs, int njobs, int block, int lpq,
-                       const float* px, const float* py, const float* pz, const PairState* st, const uint32_t* off,
-                       const uint8_t* pyr, const float4* qs4, const unsigned long long* mask, const int32_t* fb_miss,
+void launch_nns_global(const PairDev* pd, const BlockJob* jobs, int npairs, int njobs, int block, int lpq, bool sorted,
+                       const float* px, const float* py, const float* pz, const float4* ps4, const PairState* st,
+                       const uint32_t* off, const uint8_t* pyr, const float4* qs4, const unsigned long long* mask, const int32_t* fb_miss,
                        int32_t* nn_idx, float* nn_d2, int32_t* n_fallback, hipStream_t s);
 void launch_solve(const PairDev* pd, int npairs, const int32_t* fold_begin, int32_t nunits, const double* fpart,
                   const unsigned long long* fctr, PairState* st, int32_t* fb_count, const uint32_t* fb_list,
