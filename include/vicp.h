@@ -292,7 +292,7 @@ int vicp_register_batched(const vicp_grid* g, const float* px, const float* py, 
  * without a finite distance, or blocks that did not meet).  NONE before the
  * first, and after one without iterations or source points.  Every form gives
  * the same correspondences and counts, and the same poses to the last bit,
- * except where 64 queries' global searches meet more than 2^18 points in
+ * except where 64 queries' global searches meet more than 2^24 points in
  * crowded voxels: the moment sums then come in another order. */
 #define VICP_FORM_NONE 0
 #define VICP_FORM_LOOP 1

@@ -220,6 +220,7 @@ __device__ __forceinline__ void consider(const float4& q, float sx, float sy, fl
 // the direct layout 20 to 30 ms, now 4.3 (9.3).
 constexpr float kBoundSlack = 1.0f - 1e-4f;
 constexpr uint32_t kSerialPoints = 96;   // points a lane scans alone; above that the wave scans voxel by voxel
+constexpr uint32_t kSerialCost = 2048;   // what a round of over a quarter of them costs a small budget: 8 rounds of loads
 constexpr int kN = 2;                    // rows per lane and round: of a cube, or of as many bricks
 constexpr int kLoads = 4;                // point loads in flight per lane
 constexpr int kCubeMin = 2;              // the first cube's smallest radius (registration): 5^3 voxels
@@ -301,15 +302,24 @@ struct TreeBest {
         y = better ? q.y : y;
         z = better ? q.z : z;
     }
-    // distances are >= 0: their bits order as the values do
+    // Takes `points` from the budget; once that is used up the best is nearer
+    // than any bound, so that the search ends by its own tests.
+    __device__ __forceinline__ void spend(uint32_t& budget, uint32_t points)
+    {
+        budget -= min(points, budget);
+        d = budget ? d : -1.0f;
+        wave = budget ? wave : -1.0f;
+    }
+    // distances are >= 0: their bits order as the values do (and that of -1, in
+    // all lanes, is itself)
     __device__ __forceinline__ void combine() { wave = __uint_as_float(wave_min_dpp(__float_as_uint(d))); }
 };
 
 // The voxels of a brick (of which (x0, y0, z0) is the first) nearest first, each
 // scanned by the whole wave, with its row where the row is one round of loads.
-// False when the budget is used up (kGiveUp).
+// kGiveUp: within the budget.
 template <bool kGiveUp>
-__device__ __forceinline__ bool crowd_brick(const PairDev& P, const TreeBox& b, const uint32_t* __restrict__ off,
+__device__ __forceinline__ void crowd_brick(const PairDev& P, const TreeBox& b, const uint32_t* __restrict__ off,
                                             const float4* __restrict__ qs4, int x0, int y0, int z0, TreeBest& t,
                                             uint32_t& budget)
 {
@@ -333,8 +343,8 @@ __device__ __forceinline__ bool crowd_brick(const PairDev& P, const TreeBox& b, 
         const uint32_t cn = (uint32_t)__builtin_amdgcn_readlane((int)ev.y, L);
         left &= ~((uint32_t)__builtin_amdgcn_readlane((int)rw.y, L) <= kLoads * kWave ? 0xFull << (L & ~3) : 1ull << L);
         if (kGiveUp) {
-            budget -= min(cn, budget);
-            if (budget == 0u) return false;
+            t.spend(budget, cn);
+            if (budget == 0u) break;
         }
         for (uint32_t k = lane; k < cn; k += kLoads * kWave) {
             float4 q[kLoads];
@@ -345,7 +355,6 @@ __device__ __forceinline__ bool crowd_brick(const PairDev& P, const TreeBox& b, 
         }
         t.combine();
     }
-    return true;
 }
 
 // What a search does among crowded voxels: scan them, scan them within the
@@ -507,7 +516,10 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
             own[u] = e[u].y > first ? ((e[u].y - first - 1u) >> sh) + 1u : 0u;
             total += own[u];
         }
-        if (__ballot(total > kSerialPoints) == 0ull) {
+        const bool some = __ballot(total > kSerialPoints / 4) != 0ull;
+        const bool crowd = some && __ballot(total > kSerialPoints) != 0ull;
+        if (kCrowd == kCrowdBudget && some && !crowd && budget <= kStepBudget) t.spend(budget, kSerialCost);
+        if (!crowd) {
             for (uint32_t t0 = 0; t0 < total; t0 += kLoads) {
                 float4 q[kLoads];
 #pragma unroll
@@ -536,7 +548,7 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
             for (; bricks; bricks >>= 8) {   // uniform
                 const int pick = (int)(bricks & 0xFFu) - 1;
                 const int x0 = 4 * (4 * nx + (pick & 3)), y0 = 4 * (4 * ny + ((pick >> 2) & 3)), z0 = 4 * (4 * nz + (pick >> 4));
-                if (!crowd_brick<kCrowd == kCrowdBudget>(P, b, off, qs4, x0, y0, z0, t, budget)) return false;
+                crowd_brick<kCrowd == kCrowdBudget>(P, b, off, qs4, x0, y0, z0, t, budget);
             }
         }
         t.combine();
@@ -549,7 +561,7 @@ __device__ __forceinline__ bool tree_nearest(const PairDev& P, const uint32_t* _
             if (outside(lo, hi) * kBoundSlack > t.wave) break;
         }
     }
-    if (!(t.wave < INFINITY)) return false;
+    if (!(t.wave < INFINITY) || (kCrowd == kCrowdBudget && t.wave < 0.0f)) return false;
     // the lowest index among the lanes at the best distance
     const uint32_t j = wave_min_dpp(t.d == t.wave ? t.j : 0xFFFFFFFFu);
     const int owner = __ffsll((long long)__ballot(t.d == t.wave && t.j == j)) - 1;

@@ -469,8 +469,17 @@ constexpr int kLoopMaxBlocks = 512;
 // tenth without counterpart) 30 steps take 13.4 ms against 28.8, by its balanced
 // global searches; with seven (1.8M points) it took 3.5 ms
 // for 30 steps against 2.6: the launch-per-step search then has twice the waves
-// in flight on each compute unit, and its launches no longer count.
+// in flight on each compute unit, and its launches no longer count.  Between, on a
+// 64^3 grid over a room of 226,000, four lanes: 25.9 against 29.4 us with two units,
+// 35.8 and 36.5 with three, 41.7 and 43.1 with four, 60.1 and 56.0 with six.
 constexpr int64_t kLoopRounds = 2;
+// One on a crowded grid, whose steps are the search's time and nothing else: a
+// 16^3 grid over the same room, four lanes, 400 units in pairs take 200.8 us,
+// 155.6 in launches, and 8^3 499 and 411; with 7 points a voxel (32^3) 59.7 and
+// 49.8, with 3 34.6 and 33.8.
+constexpr int64_t kLoopRoundsCrowded = 1;
+// A crowded grid: its voxels hold this many points on average.
+constexpr int64_t kCrowdedPoints = 4;
 // Waves per search block (128, 256 or 512 threads): the search writes one
 // moment record per wave.
 constexpr int kNumWpb = 3;
@@ -1015,6 +1024,8 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
                            g->nfjobs[tab][wpb_index(g->nns_block)], g->npart, g->ctr, g->fpart, g->fctr, s);
 }
 
+bool crowded_grid(const vicp_grid* g) { return g->n_total >= kCrowdedPoints * g->V_total; }
+
 // Whether a single search buckets its source by target voxel first.  The five
 // launches of that cost about 20 us with 100,000 queries and 150 with 900,000,
 // more than they save where voxels hold few points (a room of 226,000: 35 us
@@ -1026,8 +1037,8 @@ bool queue_search(vicp_grid* g, const float* px, const float* py, const float* p
 // against 49 us with 40,000 queries at 10 points a voxel).
 bool bucket_single_search(const vicp_grid* g)
 {
-    const double mean = (double)g->n_total / (double)g->V_total;
-    return g->sort_src && mean >= 4.0 && g->m_total >= 50000 && mean * (double)g->m_total >= 1.5e6;
+    return g->sort_src && crowded_grid(g) && g->m_total >= 50000 &&
+           (double)g->n_total * (double)g->m_total >= 1.5e6 * (double)g->V_total;
 }
 
 // The correspondences of every pair at the poses in g->st and (unless null)
@@ -2033,7 +2044,7 @@ int loop_fit(const vicp_grid* g, int capacity, std::vector<int64_t>& U, int64_t&
     };
     while (r < most && blocks(r) > capacity) ++r;
     const int64_t nb = blocks(r);
-    if (nb > capacity || r > kLoopRounds) return 0;
+    if (nb > capacity || r > (crowded_grid(g) ? kLoopRoundsCrowded : kLoopRounds)) return 0;
     for (int p = 0; p < B; ++p)   // a pair on one block keeps its units' sums there
         if (U[p] > loop_alone_units() && loop_pair_blocks(U[p], r) == 1) return 0;
     return (int)nb;
@@ -2081,15 +2092,15 @@ int loop_plan(vicp_grid* g, int capacity, hipStream_t s)
     return nb;
 }
 
-// What the launch-per-step search may scan of crowded voxels, by whether the
-// loop could take the same registration.
+// What the launch-per-step search may scan of crowded voxels, by the grid and by
+// whether the loop could take the same registration.
 void set_step_budget(vicp_grid* g)
 {
     std::vector<int64_t> U;
     int64_t r = 0;
     int dev = -1;
     g->step_budget = kRareBudget;
-    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices &&
+    if (crowded_grid(g) && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices &&
         loop_fit(g, loop_capacity(dev, g->nns_lpq, g->sort_src), U, r) == 0)
         g->step_budget = kStepBudget;
 }

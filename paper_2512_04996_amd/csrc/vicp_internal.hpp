@@ -538,13 +538,13 @@ void launch_nns_local(const PairDev* pd, const BlockJob* jobs, int njobs, int bl
 // Among crowded voxels a wave of the registration search scans at most `budget`
 // points for its global searches; the rest of them go to the exhaustive search,
 // which has the whole device, while the wave resolves up to 64 one after the
-// other.  Sources that the resident loop never takes: kStepBudget (40 rounds of
-// loads).  200,000 points on a 16^3 grid, 180 queries far outside, 10 steps: 2.9
+// other.  Crowded grids and sources that the resident loop never takes:
+// kStepBudget (40 rounds of loads).  200,000 points on a 16^3 grid, 180 queries far outside, 10 steps: 2.9
 // ms so (4 lanes), 6.2 all in place; but with 18,000 of them 33 against 8, so
-// after a step with more than kManyMisses, and for sources that the loop may
-// take too, whose sums must come in its order, kRareBudget (0.4 ms), which only
-// extremes reach.
-constexpr uint32_t kStepBudget = 10240, kRareBudget = 1u << 18;
+// after a step with more than kManyMisses, on other grids, where few voxels are
+// crowded, and for sources that the loop may take too, whose sums must come in its
+// order, kRareBudget (25 ms), which only extremes reach.
+constexpr uint32_t kStepBudget = 10240, kRareBudget = 1u << 24;
 constexpr int32_t kManyMisses = 4096;
 // The search of every query over every target: `part` holds a word per source
 // point (of all pairs: `total`) and split of the targets.  The splits are

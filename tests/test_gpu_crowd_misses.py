@@ -79,7 +79,7 @@ def test_crowded_voxels_far_and_near(dims, counts, copies):
 
 def test_a_wave_past_its_budget_lists_its_queries():
     rng = np.random.default_rng(2)
-    n, m = 60000, 640     # 64 queries of a wave, each with 60,000 points to look at
+    n, m = 300000, 640     # 64 queries of a wave, each with 300,000 points to look at
     q = np.concatenate([rng.uniform(3.01, 3.99, (3, n)), rng.uniform(0.1, 15.9, (3, 50))], 1).astype(np.float32)
     p = (rng.uniform(-0.2, 0.2, (3, m)) + np.array([[3.5], [3.5], [7.0]])).astype(np.float32)
     g = build_grid_fixed(dev(q), (0.0, 0.0, 0.0), 1.0, (16, 16, 16), 1).dilate(0)

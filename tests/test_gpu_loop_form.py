@@ -1,6 +1,6 @@
 """Which form a registration takes: the resident loop for every source whose
-units (16 wave records) are at most two per block of the device, launches per
-step past that and for the forms that have no loop, and a hand-over for queries
+units (16 wave records) are at most two per block of the device (one on a grid
+of 4 points a voxel or more), launches per step past that and for the forms that have no loop, and a hand-over for queries
 without a finite distance.  The comparisons of the two forms rest on this."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ if not torch.cuda.is_available():
 
 from paper_2512_04996_amd._lib import (FORM_HANDED_OVER, FORM_LOOP, FORM_NONE, FORM_STEPS,  # noqa: E402
                                        VicpError)
-from paper_2512_04996_amd.api import build_grid_batched, prof_enable, prof_reset  # noqa: E402
+from paper_2512_04996_amd.api import build_grid_batched, build_grid_fixed, prof_enable, prof_reset  # noqa: E402
 
 
 def dev(a):
@@ -58,6 +58,19 @@ def test_batches(ms, form):
     g = grid(q, ms)
     g.register(dev(p), 3, m_per_pair=list(ms))
     assert g.last_form == form
+
+
+@pytest.mark.parametrize("n,crowded", [(4 * 4096 - 1, False), (4 * 4096, True)])
+def test_crowded_grids_take_one_unit_a_block(n, crowded):
+    cus = min(torch.cuda.get_device_properties(0).multi_processor_count, 512)
+    rng = np.random.default_rng(n)
+    q = rng.uniform(0, 16, (3, n))
+    g = build_grid_fixed(dev(q), (0.0, 0.0, 0.0), 1.0, (16, 16, 16), 2).dilate(2)
+    g.set_schedule(256, 8, True, 64)
+    for m, form in ((128 * cus, FORM_LOOP), (128 * cus + 1, FORM_STEPS if crowded else FORM_LOOP)):
+        p = q[:, rng.integers(0, n, m)] + rng.normal(0, 0.1, (3, m))
+        g.register(dev(p), 2)
+        assert g.last_form == form, m
 
 
 def test_forms_without_a_loop_and_hand_over():
