@@ -31,11 +31,14 @@
 // orders a flag after its data.  A unit's sums are overwritten only after the
 // next pose, which the first block publishes after it has read them all.
 //
-// Every wait ends: a block that has waited kLoopPatience ticks raises the
-// abort word (to one more than this call's tag), which every wait reads, and
-// all blocks return; the host then runs the launch-per-step form.  The host
-// launches at most as many blocks as fit the device at once, and one such loop
-// per device at a time.
+// Every wait ends: a block that has waited for `patience` ticks, or for
+// `arrive` ticks while a block of the launch has not begun, raises the abort
+// word (its lower half to one more than this call's tag, the upper to the
+// reason), which every wait reads, and all blocks return; the host then runs the
+// launch-per-step form.  The host launches at most as many blocks as fit the
+// device at once, and one such loop per device at a time; blocks may still not
+// all begin where another process' or another stream's kernels hold compute
+// units, which a block sees after 2 ms in which it waits.
 #include "search_dev.hpp"
 #include "solve_dev.hpp"
 #include "vicp_internal.hpp"
@@ -49,7 +52,6 @@ constexpr int kLoopWaves = kUnitRecords;
 constexpr int kSumCols = kMoments + 3;           // moments, candidates, dilated lookups, global searches
 constexpr int kGather = 256;                     // units gathered per round
 constexpr int kGatherLoads = (kGather * kLoopWords + kLoopThreads - 1) / kLoopThreads;
-constexpr unsigned long long kLoopPatience = 100000000ull;   // ticks of the 100 MHz clock: 1 s
 static_assert(kLoopWords == 2 * kSumCols && kSumCols * kUnitSlices <= kLoopThreads && kGather % kGroupSpan == 0,
               "message and gather layout");
 
@@ -199,17 +201,21 @@ __device__ __attribute__((noinline)) uint2 block_crowd(const float4* qs4, uint32
     return make_uint2(__float_as_uint(bd), bk);
 }
 
-__device__ __forceinline__ void raise_abort(unsigned long long* word, uint32_t tag)
+__device__ __forceinline__ void raise_abort(unsigned long long* word, uint32_t tag, uint32_t reason)
 {
-    __hip_atomic_store(word, (unsigned long long)(tag + 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(word, ((unsigned long long)reason << 32) | (tag + 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+typedef const __attribute__((address_space(4))) LoopArgs* LoopArgsPtr;
 
 // One pass of lane-wise polling: true when every lane's word carries the tag
 // (lanes that have none pass ok = true); false when the loop is to stop.
-__device__ __forceinline__ bool wait_over(bool ok, unsigned long long t0, unsigned long long* abort_word, uint32_t tag)
+__device__ __forceinline__ bool wait_over(bool ok, unsigned long long t0, LoopArgsPtr B, uint32_t tag)
 {
     if (__ballot(!ok) == 0ull) return true;
-    if (__builtin_amdgcn_s_memrealtime() - t0 > kLoopPatience) raise_abort(abort_word, tag);
+    const unsigned long long waited = __builtin_amdgcn_s_memrealtime() - t0;
+    if (waited > B->arrive && (waited > B->patience || ld_agent(B->begun) < B->begun_all))
+        raise_abort(B->abort_word, tag, kAbortWait);
     __builtin_amdgcn_s_sleep(1);
     return false;
 }
@@ -240,6 +246,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
         sh.Rt[threadIdx.x] = S.Rt[threadIdx.x];
     }
     if (threadIdx.x == 0) {
+        __hip_atomic_fetch_add(A.begun, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sh.geo = GridGeom{P.ox, P.oy, P.oz, P.inv, P.fDx, P.fDy, P.fDz, P.cx, P.cy, P.cz, (uint32_t)P.Dx, (uint32_t)P.Dy};
         sh.done = 0;
         sh.misses = 0;
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
         asm volatile("" : "+v"(tid));
         // the arguments that only some blocks or iterations use are read where
         // they are used, through a pointer that is opaque too
-        auto B = (const __attribute__((address_space(4))) LoopArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        auto B = (LoopArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(B));
         const int lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid / kWave), sub = lane % LPQ;
         if (k > 0 && !alone && !solver) {
@@ -268,8 +275,8 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
                 bool over = false, quit = false;
                 while (!over && !quit) {
                     v = lane < kPoseWords ? ld_agent(pmsg + lane) : (lane == kWave - 1 ? ld_agent(B->abort_word) : 0ull);
-                    quit = __ballot(lane == kWave - 1 && v == (unsigned long long)(A.tag + 1u)) != 0ull;
-                    over = wait_over(lane >= kPoseWords || (uint32_t)(v >> 32) == tag, t0, B->abort_word, A.tag);
+                    quit = __ballot(lane == kWave - 1 && (uint32_t)v == A.tag + 1u) != 0ull;
+                    over = wait_over(lane >= kPoseWords || (uint32_t)(v >> 32) == tag, t0, B, A.tag);
                 }
                 if (lane < 12) sh.pose[lane] = __uint_as_float((uint32_t)v);
                 if (lane == 12) sh.done = (int32_t)(uint32_t)v;
@@ -391,7 +398,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
                 }
                 if (tid == 0) {
                     sh.misses = 0;
-                    if (sh.stop) raise_abort(B->abort_word, A.tag);
+                    if (sh.stop) raise_abort(B->abort_word, A.tag, kAbortQuery);
                 }
             }
             if (w == 0 && lane < kSumCols) {
@@ -438,8 +445,8 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
 #pragma unroll
                     for (int e = 0; e < kGatherLoads; ++e)
                         ok &= tid + e * kLoopThreads >= n * kLoopWords || (uint32_t)(v[e] >> 32) == tag;
-                    quit = __ballot(lane == 0 && ab == (unsigned long long)(A.tag + 1u)) != 0ull;
-                    over = wait_over(ok, t0, B->abort_word, A.tag);
+                    quit = __ballot(lane == 0 && (uint32_t)ab == A.tag + 1u) != 0ull;
+                    over = wait_over(ok, t0, B, A.tag);
                 }
                 if (!over && lane == 0) sh.stop = 1;
                 uint32_t* stage = reinterpret_cast<uint32_t*>(&sh.stage[0][0]);

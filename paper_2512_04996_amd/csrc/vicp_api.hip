@@ -634,6 +634,9 @@ struct vicp_grid {
     unsigned long long *loop_msg = nullptr, *loop_pose = nullptr;
     int64_t loop_units = 0;
     uint32_t loop_tag = 0;
+    uint64_t loop_begun = 0;        // blocks of all loops launched since the layout
+    uint64_t loop_arrive = kLoopArrive, loop_patience = kLoopPatience;
+    int loop_rest = 0;              // registrations to run without the loop (kLoopRest)
     LoopJob* loop_jobs = nullptr;   // a batch's blocks, for loop_lpq lanes per query
     int loop_lpq = 0, loop_blocks = 0;
     uint32_t step_budget = kRareBudget;   // of the launch-per-step search's waves (kStepBudget)
@@ -864,7 +867,7 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
         g->o_deg = g->o_fb + sizeof(int32_t) * bk;
         g->o_flags = g->o_deg + sizeof(int32_t) * bk;
         g->o_abort = a8(g->o_flags + sizeof(int32_t) * B);
-        g->res_bytes = g->o_abort + 8;
+        g->res_bytes = g->o_abort + 16;   // the abort word and the count of blocks begun
         if (g->h_res_cap < g->res_bytes) {
             if (g->h_res) (void)hipHostFree(g->h_res);
             g->h_res = nullptr;
@@ -932,6 +935,7 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
     g->loop_pose = g->loop_msg + g->loop_units * kLoopWords;
     g->loop_lpq = 0;
     g->loop_tag = 0;
+    g->loop_begun = 0;
     g->st = (PairState*)g->res;
     g->rmse_hist = (double*)(g->res + g->o_rmse);
     g->ctr_hist = (unsigned long long*)(g->res + g->o_ctr);
@@ -950,7 +954,7 @@ int ensure_source(vicp_grid* g, const int64_t* m_per_pair, int K, hipStream_t s)
     fill_pairdev(g, pd);
     VICP_HIP(hipMemcpyAsync(g->d_pd, pd.data(), sizeof(PairDev) * B, hipMemcpyHostToDevice, s));
     VICP_HIP(hipMemcpyAsync(d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice, s));
-    launch_clear4((uint32_t*)g->fb_count, 2 * B, g->loop_msg, loop_words, (uint32_t*)(g->res + g->o_abort), 2, nullptr, 0, s);
+    launch_clear4((uint32_t*)g->fb_count, 2 * B, g->loop_msg, loop_words, (uint32_t*)(g->res + g->o_abort), 4, nullptr, 0, s);
     VICP_HIP(hipStreamSynchronize(s));   // the host tables go out of scope
     g->m_total = mt;
     g->K_cap = Kc;
@@ -1995,6 +1999,9 @@ int capture_into(vicp_grid* g, vicp_grid::Captured& c, const std::vector<uintptr
 // could each hold what the other waits for.  A call that finds it taken runs
 // the launch-per-step form.
 constexpr int kMaxDevices = 64;
+// Registrations that a grid runs without the loop after one whose blocks did not
+// meet: 2 ms lost in one of 33.
+constexpr int kLoopRest = 32;
 std::mutex g_loop_mu[kMaxDevices];
 
 // Blocks of the loop kernel that fit the device together (0 when unknown).
@@ -2015,6 +2022,22 @@ int loop_capacity(int dev, int lpq, bool sorted)
         c = std::min(per * cus, kLoopMaxBlocks);
     }
     return c;
+}
+
+// Whether the stream's kernels may use every compute unit (the loop's blocks
+// might otherwise not all be resident).
+bool whole_device(hipStream_t s, int dev)
+{
+    constexpr int kWords = 32;
+    uint32_t mask[kWords] = {};
+    int cus = 0, bits = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus > 32 * kWords ||
+        hipExtStreamGetCUMask(s, (uint32_t)(cus + 31) / 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    for (uint32_t w : mask) bits += __builtin_popcount(w);
+    return bits == 0 || bits >= cus;
 }
 
 // Blocks of pair p's U units when every block takes at most r of them.
@@ -2137,6 +2160,11 @@ void queue_loop(vicp_grid* g, const float* px, const float* py, const float* pz,
     a.fb_hist = g->fb_hist;
     a.deg_hist = g->deg_hist;
     a.ctr_hist = g->ctr_hist;
+    a.begun = a.abort_word + 1;
+    g->loop_begun += (uint64_t)nloop;
+    a.begun_all = g->loop_begun;
+    a.arrive = g->loop_arrive;
+    a.patience = g->loop_patience;
     a.eps = eps;
     a.tag = g->loop_tag;
     a.K = K;
@@ -2214,7 +2242,8 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
     if (allow_loop && !all_global && !direct && !g_prof.on && !capturing(s) && hipGetDevice(&dev) == hipSuccess &&
         dev >= 0 && dev < kMaxDevices) {
         loop_lock = std::unique_lock<std::mutex>(g_loop_mu[dev], std::try_to_lock);
-        if (loop_lock.owns_lock()) nloop = loop_plan(g, loop_capacity(dev, g->nns_lpq, g->sort_src), s);
+        if (g->loop_rest > 0) --g->loop_rest;
+        else if (loop_lock.owns_lock() && whole_device(s, dev)) nloop = loop_plan(g, loop_capacity(dev, g->nns_lpq, g->sort_src), s);
     }
     if (all_global) plan_exhaustive(g, s);
     g->last_form = nloop > 0 ? VICP_FORM_LOOP : (allow_loop ? VICP_FORM_STEPS : VICP_FORM_HANDED_OVER);
@@ -2265,10 +2294,12 @@ int register_impl(vicp_grid* g, const float* px, const float* py, const float* p
     VICP_HIP(wait_tags((const uint32_t*)g->h_res + rwords, npub, 1, g->res_gen, s));
     if (g_prof.on) VICP_HIP(hipStreamSynchronize(s));
     const char* hb = (const char*)g->h_res;
-    if (nloop > 0 && *(const unsigned long long*)(hb + g->o_abort) == (unsigned long long)(g->loop_tag - (uint32_t)K + 1u)) {
+    const unsigned long long gave_up = *(const unsigned long long*)(hb + g->o_abort);
+    if (nloop > 0 && (uint32_t)gave_up == g->loop_tag - (uint32_t)K + 1u) {
         // the loop gave up (blocks that never met, or a query without a finite
         // distance): again by the launch-per-step form
         loop_lock.unlock();
+        if ((uint32_t)(gave_up >> 32) == kAbortWait) g->loop_rest = kLoopRest;
         return register_impl(g, px, py, pz, m_per_pair, o, Rt_io, stats, s, false, false);
     }
     const PairState* hst = (const PairState*)hb;
@@ -2704,6 +2735,16 @@ __global__ void k_synthetic_misses(const PairDev* __restrict__ pd, int npairs, i
 }  // namespace
 
 extern "C" {
+
+// For tests: how long a block of the grid's loop waits (ticks of 10 ns) for a
+// block that has not begun, and for any; not part of the interface.
+int vicp_test_loop_waits(vicp_grid* g, uint64_t arrive, uint64_t patience)
+{
+    if (!g) return fail(VICP_ERR_INVALID_ARG, "null grid");
+    g->loop_arrive = arrive;
+    g->loop_patience = patience;
+    return VICP_OK;
+}
 
 int vicp_autotune_cache_clear(void)
 {

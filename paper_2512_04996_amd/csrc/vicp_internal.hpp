@@ -637,13 +637,19 @@ struct LoopArgs {
     int32_t* nn_idx;
     float* nn_d2;
     unsigned long long *msg, *pose_msg, *abort_word;
+    unsigned long long* begun;      // blocks begun, over all launches of the grid
     double* rmse_hist;
     int32_t *fb_hist, *deg_hist;
     unsigned long long* ctr_hist;
     double eps;
+    unsigned long long begun_all;   // ... and their number when all of this launch have
+    unsigned long long arrive, patience;   // ticks of the 100 MHz clock
     uint32_t tag;   // messages of iteration k carry tag + k + 1
     int32_t K, early_stop;
 };
+// Why a loop gave up: a query without a finite distance, or a wait.
+constexpr uint32_t kAbortQuery = 0, kAbortWait = 1;
+constexpr unsigned long long kLoopArrive = 200000ull, kLoopPatience = 100000000ull;   // 2 ms, 1 s
 const void* loop_kernel(int lpq, bool sorted);
 int loop_threads();
 int loop_alone_units();   // most units of a pair served by one block
