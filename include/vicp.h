@@ -350,10 +350,15 @@ int vicp_grid_free(vicp_grid* g);
  *     (the histogram it leaves is the same);
  *   - on a dilated grid of 1 to 4 rings, the dilation's form and tile shape,
  *     re-running the dilation (which leaves the same grid);
- *   - the search (see vicp_get_schedule) in its registration form at the
- *     identity pose; the source-bucketing pass serves `searches_per_plan`
- *     searches (1 for vicp_nns, the iteration count for vicp_register) and is
- *     charged at that rate;
+ *   - the search (see vicp_get_schedule) at the identity pose: for each number
+ *     of lanes and source order the block size and candidate loop by single
+ *     searches in the registration form, and the lanes and order by eight
+ *     iterations in the form that the registration would run (for
+ *     `searches_per_plan` above 1), or by those searches (for 1: vicp_nns and
+ *     the loss run the search without the moment sums, and bucket their source
+ *     by a rule of their own); the source-bucketing pass serves
+ *     `searches_per_plan` searches (1 for vicp_nns, the iteration count for
+ *     vicp_register) and is charged at that rate;
  *   - the global search's block count on a load of listed queries (the
  *     first max(256, m/64) sources of each pair) charged once per
  *     `searches_per_plan` searches, beside the fold it also runs.

@@ -2852,61 +2852,94 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
         g->dil_shape = bs.dil_shape;
         g->ring_block = bs.ring_block;
     }
-    // (3) the search: for single searches in its registration form at the
-    // identity pose, for registrations as kTuneIters iterations from there, in
-    // the form the registration would run (the resident loop where it applies,
-    // which has one block size and candidate loop)
+    // (3) the search.  Its block size and candidate loop are those whose search in
+    // the registration form, alone and at the identity pose, is the fastest, for
+    // each number of lanes and order: the launch-per-step form runs under them
+    // (large sources, the direct layout, timing on, a loop that gave up), and the
+    // resident loop does not use them.  The lanes and the order are then those of
+    // the fastest kTuneIters iterations in the form that the registration would
+    // run, or for single searches of the fastest search.
     const float plan_ms = timed([&] { queue_plan(g, px, py, pz, s, true); });
-    int best_bs = 256, best_lpq = 4, best_fg = g->fb_grid;
-    bool best_sorted = true;
+    Sched picked = sched_of(g);
     float best = 1e30f;
-    int best_mode = 0;
     int dev = -1;
     std::unique_lock<std::mutex> loop_lock;
-    if (registers && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices)
+    if (registers && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && whole_device(s, dev))
         loop_lock = std::unique_lock<std::mutex>(g_loop_mu[dev], std::try_to_lock);
+    // the search kernel's own time, the least of five after one untimed: queued
+    // back to back, the launches beside it hide differences of a few microseconds
+    auto search_alone = [&]() -> float {
+        float least = 1e30f;
+        for (int rep = 0; rep < 6; ++rep) {
+            launch_fill_u32((uint32_t*)g->fb_count, 0u, 2 * g->B, s);
+            ExtEvents ext;
+            ext.a = a;
+            ext.b = b;
+            t_ext = &ext;
+            queue_search(g, px, py, pz, nullptr, nullptr, s, true);
+            t_ext = nullptr;
+            (void)hipEventSynchronize(b);
+            float ms = 0.0f;
+            if (rep > 0 && ext.used && hipEventElapsedTime(&ms, a, b) == hipSuccess) least = std::min(least, ms);
+        }
+        return least;
+    };
+    // kTuneIters iterations; gave_up: whether a loop among them did
+    auto iterations = [&](int nloop, bool* gave_up) -> float {
+        const uint32_t tag0 = g->loop_tag;
+        const float t = timed_raw([&] {
+            queue_start(g, rt.data(), px, py, pz, s);
+            if (nloop > 0) queue_loop(g, px, py, pz, nloop, kTuneIters, 0, 0.0, nullptr, nullptr, s);
+            for (int k = 0; k < kTuneIters && nloop == 0; ++k)
+                (void)queue_iteration(g, px, py, pz, k, kTuneIters, 0, 0.0, s, true, false, false, nullptr, nullptr);
+        }, 1);
+        unsigned long long word = 0;
+        if (nloop > 0 && hipMemcpy(&word, g->res + g->o_abort, sizeof(word), hipMemcpyDeviceToHost) != hipSuccess)
+            word = ~0ull;
+        *gave_up = nloop > 0 && ((uint32_t)word - tag0 - 1u < g->loop_tag - tag0 || word == ~0ull);
+        return t / (float)kTuneIters;
+    };
     for (int sorted = 0; sorted < 2; ++sorted)
-        for (int bs : {128, 256, 512})
-            for (int lpq : {1, 2, 4, 8})
+        for (int lpq : {1, 2, 4, 8}) {
+            g->sort_src = sorted != 0;
+            g->nns_lpq = lpq;
+            set_step_budget(g);
+            float t = 1e30f;
+            int bs_best = 256, mode_best = 0;
+            for (int bs : {128, 256, 512})
                 for (int mode = 0; mode < 2; ++mode) {
                     g->nns_block = bs;
-                    g->nns_lpq = lpq;
-                    g->sort_src = sorted != 0;
                     g->search_mode = mode;
-                    set_step_budget(g);
-                    const int nloop = loop_lock.owns_lock() ? loop_plan(g, loop_capacity(dev, lpq, g->sort_src), s) : 0;
-                    if (nloop > 0 && (bs != 128 || mode != 0)) continue;
-                    float t;
-                    if (registers) {
-                        t = timed_raw([&] {
-                                queue_start(g, rt.data(), px, py, pz, s);
-                                if (nloop > 0)
-                                    queue_loop(g, px, py, pz, nloop, kTuneIters, 0, 0.0, nullptr, nullptr, s);
-                                for (int k = 0; k < kTuneIters && nloop == 0; ++k)
-                                    (void)queue_iteration(g, px, py, pz, k, kTuneIters, 0, 0.0, s, true, false, false,
-                                                          nullptr, nullptr);
-                            }, 1) / (float)kTuneIters;
-                    } else {
-                        t = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true); });
-                    }
-                    t += sorted ? plan_ms / (float)searches_per_plan : 0.0f;
-                    if (t < kMargin * best) {
-                        best = t;
-                        best_bs = bs;
-                        best_lpq = lpq;
-                        best_sorted = sorted != 0;
-                        best_mode = mode;
+                    const float ts = search_alone();
+                    if (ts < kMargin * t) {
+                        t = ts;
+                        bs_best = bs;
+                        mode_best = mode;
                     }
                 }
+            g->nns_block = bs_best;
+            g->search_mode = mode_best;
+            if (registers) {
+                // a loop that gives up did not run its iterations
+                bool gave_up = false;
+                const int nloop = loop_lock.owns_lock() ? loop_plan(g, loop_capacity(dev, lpq, g->sort_src), s) : 0;
+                t = iterations(nloop, &gave_up);
+                if (gave_up) t = iterations(0, &gave_up);
+            }
+            t += sorted ? plan_ms / (float)searches_per_plan : 0.0f;
+            if (t < kMargin * best) {
+                best = t;
+                picked = sched_of(g);
+            }
+        }
     if (loop_lock.owns_lock()) {
         VICP_HIP(hipStreamSynchronize(s));   // no loop is left running when the device's turn passes on
         loop_lock.unlock();
     }
     queue_start(g, rt.data(), px, py, pz, s);
-    g->nns_block = best_bs;
-    g->nns_lpq = best_lpq;
-    g->sort_src = best_sorted;
-    g->search_mode = best_mode;
+    apply_sched(g, picked);
+    set_step_budget(g);
+    int best_fg = g->fb_grid;
     // (4) the global search's blocks: the fold every iteration runs, plus a
     // listed-query load once per bucketing pass
     {
