@@ -691,6 +691,10 @@ struct vicp_grid {
             release(a, s);
             a.buf.bytes = a.need + spare;
             a.buf.p = mem.get(a.buf.bytes, s);
+            if (!a.buf.p && spare) {   // near the end of the memory: what it needs
+                a.buf.bytes = a.need;
+                a.buf.p = mem.get(a.buf.bytes, s);
+            }
             if (!a.buf.p) {
                 a.buf.bytes = 0;
                 return false;
