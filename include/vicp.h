@@ -251,7 +251,7 @@ int vicp_nns_batched(const vicp_grid* g, const float* px, const float* py, const
  * with every intermediate (the pose, the work tables, the search waves' masks
  * of queries for the global search) in one fixed device array that the
  * library holds on each GPU it runs on until the process ends
- * (14,713,600 bytes, sized for VICP_NOALLOC_MAX_QUERIES source points),
+ * (1,573,696 bytes, sized for VICP_NOALLOC_MAX_QUERIES source points),
  * instead of the grid's workspace.  Same arguments, outputs and results as vicp_nns (bit for bit:
  * the same search kernels, over the source in index order); the grid must
  * have been built beforehand (building allocates).  Allocates nothing: no

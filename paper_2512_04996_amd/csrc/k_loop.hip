@@ -50,7 +50,7 @@ namespace {
 constexpr int kLoopThreads = kWave * kUnitRecords;
 constexpr int kLoopWaves = kUnitRecords;
 constexpr int kSumCols = kMoments + 3;           // moments, candidates, dilated lookups, global searches
-constexpr int kGather = 256;                     // units gathered per round
+constexpr int kGather = kLoopAloneUnits;         // units gathered per round
 constexpr int kGatherLoads = (kGather * kLoopWords + kLoopThreads - 1) / kLoopThreads;
 static_assert(kLoopWords == 2 * kSumCols && kSumCols * kUnitSlices <= kLoopThreads && kGather % kGroupSpan == 0,
               "message and gather layout");
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kLoopThreads) void k_icp_loop(LoopArgs A)
                 for (int e = 0; e < kUnitRecords; ++e) v[e] = sh.rec[e][lane];
                 const double sum = unit_sum(v);
                 if (alone) {
-                    sh.stage[lane][u] = sum;   // U <= kGather (loop_alone_units)
+                    sh.stage[lane][u] = sum;   // U <= kGather (kLoopAloneUnits)
                 } else {
                     const uint32_t tag = A.tag + (uint32_t)k + 1u;
                     unsigned long long* out = msg + (int64_t)u * kLoopWords + 2 * lane;
@@ -531,7 +531,6 @@ const void* loop_kernel(int lpq, bool sorted)
 }
 
 int loop_threads() { return kLoopThreads; }
-int loop_alone_units() { return kGather; }
 
 void launch_loop(const LoopArgs& a, int nblocks, int lpq, bool sorted, hipStream_t s)
 {

@@ -26,9 +26,9 @@
 // resolves the query itself by an exact search of the occupancy pyramid.
 // Exhaustive search (queries without a finite distance, or behind the budget of
 // a wave among crowded voxels): the query is appended to a per-pair list and a
-// brute force over all targets resolves it; partial minima from target tiles merge through a 64-bit
-// atomic minimum of (distance bits << 32 | index), which is order-free, so
-// the result is deterministic.
+// brute force over all targets resolves it; partial minima from target tiles
+// merge through a 64-bit atomic minimum of (distance bits << 32 | index), which
+// is order-free, so the result is deterministic.
 #include <math.h>
 
 #include <algorithm>
@@ -47,14 +47,14 @@ namespace {
 // LPQ times more waves in flight to hide the load latency.
 //
 // kMom (registration): instead of writing each correspondence, each wave
-// adds the float64 moments of Eq. 1 over its locally resolved queries (sum p,
+// adds the float64 moments of Eq. 1 over the queries it resolves (sum p,
 // sum q, sum p q^T, sum |p|^2, sum |q|^2 about the grid centre, sum d, count)
 // in a fixed lane order and writes one record, with its counters
-// (candidates scanned, dilated lookups, queries sent to the global search).
+// (candidates scanned, dilated lookups, queries that needed a global search).
 // Records are wave-major: wave w of job b is record r = b * (BS / 64) + w,
-// entry j at [r * kMoments + j], counter k at [r * 3 + k].  Queries sent to
-// the global search add their moments later, once resolved.  Launch blocks
-// are mapped to jobs XCD by XCD (xcd_job).
+// entry j at [r * kMoments + j], counter k at [r * 3 + k].  Listed queries (see
+// below) add their moments in the solve.  Launch blocks are mapped to jobs XCD
+// by XCD (xcd_job, xcd_slab).
 //
 // kDirect: VANICP's monolithic layout (the comparator).  Voxel g's
 // candidates are the records of its own fixed block, at g * cap, and its
@@ -120,12 +120,9 @@ __global__ __launch_bounds__(BS) void k_nns_local(const PairDev* __restrict__ pd
     float sx = 0.0f, sy = 0.0f, sz = 0.0f;
     bool dil = false;
     // The query's load goes out unconditionally (a lane past the end reads
-    // the block's first query, which exists) and does not wait for the
-    // pair's done flag, so the two latencies overlap.  A finished pair's
-    // block runs with no active lane: it searches nothing and appends
-    // nothing, and its partials are never read (the fold and the solve skip
-    // finished pairs).  An early return would let the compiler sink the load
-    // below the flag's test.
+    // the block's first query, which exists).  Where no pair can stop early it
+    // does not wait for the pair's done flag, so the two latencies overlap; the
+    // flag then only says that a pair has no source points, which has no blocks.
     {
         const int64_t tl = (kOne ? (int64_t)0 : P.p_base) + (inrange ? t : (int64_t)job.start);
         if (kSorted) {

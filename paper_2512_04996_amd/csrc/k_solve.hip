@@ -1,7 +1,7 @@
 // k_solve.hip -- the closed-form rigid transform of Eq. 1 per pair, in
 // float64, and the ICP iteration bookkeeping (Sec. II.A; stop rule of
 // Sec. IV.A).  One block per pair reduces the moment partials that the
-// search blocks wrote, adds the queries resolved by the global search in
+// search blocks wrote, adds the queries resolved by the exhaustive search in
 // index order (both in a fixed order), then one lane forms the cross-covariance
 // H = sum (p - pbar)(q - qbar)^T = sum p q^T - m pbar qbar^T, takes its SVD
 // H = U S V^T by one-sided Jacobi, and sets R = V diag(1, 1, det(V U^T)) U^T,
@@ -47,7 +47,8 @@ __device__ __forceinline__ void add_moments(double* a, float px, float py, float
 
 // One block per pair.  (1) The pair's groups (moment-major, stride
 // nunits) are summed per moment and counter by kUnitSlices threads each, in
-// a fixed order.  (2) Queries resolved by the global search, when there are any: their list is in arbitrary order, so it
+// a fixed order.  (2) Queries resolved by the exhaustive search, when any were
+// listed: their list is in arbitrary order, so it
 // is replayed in windows of kFbWindow source indices through an LDS bitmap;
 // each thread adds the correspondences of its own 32 indices per window in
 // index order, and a fixed-order block reduction adds them to (1).  (3) The

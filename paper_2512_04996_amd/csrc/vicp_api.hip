@@ -473,6 +473,7 @@ constexpr int kLoopMaxBlocks = 512;
 // 64^3 grid over a room of 226,000, four lanes: 25.9 against 29.4 us with two units,
 // 35.8 and 36.5 with three, 41.7 and 43.1 with four, 60.1 and 56.0 with six.
 constexpr int64_t kLoopRounds = 2;
+static_assert(kLoopRounds <= kLoopAloneUnits, "a pair on one block keeps its units' sums there");
 // One on a crowded grid, whose steps are the search's time and nothing else: a
 // 16^3 grid over the same room, four lanes, 400 units in pairs take 200.8 us,
 // 155.6 in launches, and 8^3 499 and 411; with 7 points a voxel (32^3) 59.7 and
@@ -1067,8 +1068,7 @@ void queue_correspondences(vicp_grid* g, const float* px, const float* py, const
     }
     ProfScope ps("nns_global", s, cap, true);
     launch_nns_global(g->d_pd, g->jobs_p[tab], g->B, g->njobs_p[tab], g->nns_block, g->nns_lpq, sorted, px, py, pz,
-                      g->ps4, g->st, g->off,
-                      g->pyr, g->qs4, g->ctr, miss, nn_idx, nn_d2, n_fallback, s);
+                      g->ps4, g->st, g->off, g->pyr, g->qs4, g->ctr, miss, nn_idx, nn_d2, n_fallback, s);
 }
 
 // The registration form of the search with every query compared with every
@@ -1825,20 +1825,16 @@ namespace {
 constexpr int64_t kNaMaxQ = VICP_NOALLOC_MAX_QUERIES;
 constexpr int64_t kNaMinQpb = 16;                        // fewest queries per block of any schedule
 constexpr int64_t kNaMaxJobs = kNaMaxQ / kNaMinQpb;      // search blocks
-constexpr int64_t kNaMaxJobs256 = kNaMaxQ / 256;         // 256-point blocks of the result pass
+constexpr int64_t kNaMaxMasks = kNaMaxQ / 8 + 8;          // search waves: a mask word each (8 lanes a query, the last block's)
 constexpr size_t kNaOffPd = 0;                           // PairDev
 constexpr size_t kNaOffSt = 256;                         // PairState
-constexpr size_t kNaOffCnt = 512;                        // global-search count, fault flags
+constexpr size_t kNaOffCnt = 512;                        // queries that needed a global search
 constexpr size_t kNaOffJobs = 768;
-constexpr size_t kNaOffJobs256 = kNaOffJobs + sizeof(BlockJob) * kNaMaxJobs;
-constexpr size_t kNaOffCtr = kNaOffJobs256 + sizeof(BlockJob) * kNaMaxJobs256;
-constexpr size_t kNaOffList = kNaOffCtr + sizeof(unsigned long long) * 3 * kNaMaxJobs;
-constexpr size_t kNaOffKey = kNaOffList + sizeof(uint32_t) * kNaMaxQ;
-constexpr size_t kNaBytes = kNaOffKey + sizeof(unsigned long long) * kNaMaxQ;
+constexpr size_t kNaOffMask = kNaOffJobs + sizeof(BlockJob) * kNaMaxJobs;
+constexpr size_t kNaBytes = kNaOffMask + sizeof(unsigned long long) * kNaMaxMasks;
 static_assert(sizeof(PairDev) <= 256 && sizeof(PairState) <= 256, "scratch header slots");
-static_assert(kNaOffJobs256 % 256 == 0 && kNaOffCtr % 256 == 0 && kNaOffList % 256 == 0 && kNaOffKey % 256 == 0,
-              "scratch sections stay 256-byte aligned");
-static_assert(kNaBytes == 14713600, "the size the header states");
+static_assert(kNaOffMask % 256 == 0, "scratch sections stay 256-byte aligned");
+static_assert(kNaBytes == 1573696, "the size the header states");
 
 }  // namespace
 
@@ -1893,7 +1889,7 @@ __global__ void k_noalloc_setup(NaSetup a, int32_t njobs, int32_t qpb, unsigned 
         S.rot_ok = 0;
         S.misses = 0;
         int32_t* cnt = reinterpret_cast<int32_t*>(base + kNaOffCnt);
-        cnt[2] = 0;   // queries that needed a global search
+        cnt[0] = 0;
     }
     BlockJob* jobs = reinterpret_cast<BlockJob*>(base + kNaOffJobs);
     for (int64_t j = tid; j < njobs; j += (int64_t)gridDim.x * blockDim.x) jobs[j] = BlockJob{0, (int32_t)(j * qpb)};
@@ -1939,16 +1935,14 @@ int vicp_nns_noalloc(const vicp_grid* g, const float* px, const float* py, const
     const PairDev* pd = reinterpret_cast<const PairDev*>(base + kNaOffPd);
     PairState* st = reinterpret_cast<PairState*>(base + kNaOffSt);
     const BlockJob* jobs = reinterpret_cast<const BlockJob*>(base + kNaOffJobs);
-    // a word per wave of the search: at most m / 8 + 8
-    unsigned long long* mask = reinterpret_cast<unsigned long long*>(base + kNaOffKey);
+    unsigned long long* mask = reinterpret_cast<unsigned long long*>(base + kNaOffMask);
     const int setup_blocks = (int)std::min<int64_t>((njobs + 255) / 256, 256);
     hipLaunchKernelGGL(k_noalloc_setup, dim3(setup_blocks), dim3(256), 0, s, a, (int32_t)njobs, (int32_t)qpb, base);
     launch_nns_local(pd, jobs, (int)njobs, g->nns_block, g->nns_lpq, false, false, px, py, pz, nullptr, st, g->dir,
-                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, cnt + 2, nullptr, nullptr, mask, nullptr,
+                     g->off, g->pyr, g->qs4, g->qs4, nn_idx, nn_d2, nullptr, cnt, nullptr, nullptr, mask, nullptr,
                      nullptr, 0u, 0, m, 0, 0u, s);
     launch_nns_global(pd, jobs, 1, (int)njobs, g->nns_block, g->nns_lpq, false, px, py, pz, nullptr, st, g->off, g->pyr,
-                      g->qs4, mask,
-                      cnt + 2, nn_idx, nn_d2, n_fallback, s);
+                      g->qs4, mask, cnt, nn_idx, nn_d2, n_fallback, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(VICP_ERR_HIP, std::string("nns_noalloc: ") + hipGetErrorString(e));
     return VICP_OK;
@@ -2072,8 +2066,6 @@ int loop_fit(const vicp_grid* g, int capacity, std::vector<int64_t>& U, int64_t&
     while (r < most && blocks(r) > capacity) ++r;
     const int64_t nb = blocks(r);
     if (nb > capacity || r > (crowded_grid(g) ? kLoopRoundsCrowded : kLoopRounds)) return 0;
-    for (int p = 0; p < B; ++p)   // a pair on one block keeps its units' sums there
-        if (U[p] > loop_alone_units() && loop_pair_blocks(U[p], r) == 1) return 0;
     return (int)nb;
 }
 

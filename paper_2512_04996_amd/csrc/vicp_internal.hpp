@@ -652,7 +652,7 @@ constexpr uint32_t kAbortQuery = 0, kAbortWait = 1;
 constexpr unsigned long long kLoopArrive = 200000ull, kLoopPatience = 100000000ull;   // 2 ms, 1 s
 const void* loop_kernel(int lpq, bool sorted);
 int loop_threads();
-int loop_alone_units();   // most units of a pair served by one block
+constexpr int kLoopAloneUnits = 256;   // most units of a pair served by one block
 void launch_loop(const LoopArgs& a, int nblocks, int lpq, bool sorted, hipStream_t s);
 
 // differentiable loss
