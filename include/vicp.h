@@ -359,9 +359,11 @@ int vicp_grid_free(vicp_grid* g);
  *     by a rule of their own); the source-bucketing pass serves
  *     `searches_per_plan` searches (1 for vicp_nns, the iteration count for
  *     vicp_register) and is charged at that rate;
- *   - the global search's block count on a load of listed queries (the
- *     first max(256, m/64) sources of each pair) charged once per
- *     `searches_per_plan` searches, beside the fold it also runs.
+ *   - the block count of the launch that folds the moment sums and runs the
+ *     exhaustive search of listed queries: by the fold, and on a grid of four
+ *     points a voxel or more (whose searches may list queries) by a load of
+ *     such queries too (the first max(256, m/64) sources of each pair), charged
+ *     once per `searches_per_plan` searches.
  * The chosen schedule is stored per shape (pairs' point counts, grid
  * dimensions, rings, source sizes); a later call on the same shape in this
  * process takes it without timing, and with the environment variable

@@ -2936,15 +2936,16 @@ int vicp_autotune(vicp_grid* g, const float* px, const float* py, const float* p
     apply_sched(g, picked);
     set_step_budget(g);
     int best_fg = g->fb_grid;
-    // (4) the global search's blocks: the fold every iteration runs, plus a
-    // listed-query load once per bucketing pass
+    // (4) the exhaustive search's blocks: the fold every iteration runs, and on a
+    // crowded grid, whose searches list queries, such a load once per bucketing
+    // pass (elsewhere none is listed)
     {
         const int tab = table_of(g->nns_block / g->nns_lpq);
         best = 1e30f;
         for (int fg : {64, 128, 256, 512, 1024}) {
             g->fb_grid = fg;
             const float t0 = timed([&] { queue_search(g, px, py, pz, nullptr, nullptr, s, true); });
-            const float t1 = timed_raw([&] {
+            const float t1 = !crowded_grid(g) ? 0.0f : timed_raw([&] {
                 hipLaunchKernelGGL(k_synthetic_misses, dim3(g->B), dim3(256), 0, s, g->d_pd, g->B, g->fb_count,
                                    g->fb_list, g->fb_key);
                 (void)launch_fallback(g->d_pd, g->B, fg, g->qx, g->qy, g->qz, px, py, pz, g->st, g->fb_count,

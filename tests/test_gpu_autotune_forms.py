@@ -1,7 +1,8 @@
 """The autotuner and the resident loop: a loop that gives up while it is timed has
 not run its iterations, so it must not win (a query without a finite distance
 ends it in its first step), and the block size and candidate loop are tuned for
-the launches also where the loop applies.  A registration under the chosen
+the launches also where the loop applies, and no load is timed that a grid
+cannot have.  A registration under the chosen
 schedule takes at most 1.6 times the best of all schedules."""
 import time
 
@@ -17,7 +18,7 @@ if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
 from paper_2512_04996_amd._lib import FORM_HANDED_OVER, FORM_LOOP, FORM_STEPS  # noqa: E402
-from paper_2512_04996_amd.api import autotune_cache_clear, build_grid_fixed, prof_enable, prof_read, prof_reset  # noqa: E402
+from paper_2512_04996_amd.api import autotune_cache_clear, build_grid, build_grid_fixed, prof_enable, prof_read, prof_reset  # noqa: E402
 
 
 def dev(a):
@@ -56,6 +57,24 @@ def test_a_loop_that_gives_up_does_not_win():
                 g.set_schedule(block, lanes, True, 128, mode)
                 swept.append((best(), block, lanes, mode))
     assert tuned < 1.6 * min(swept)[0], (chosen, tuned, sorted(swept)[:4])
+
+
+def test_no_listed_queries_are_timed_where_none_are_listed():
+    # a fine grid lists no query with a finite distance: tuning a large source
+    # takes some 90 registrations' time; with a listed load it took 1100
+    P = synth.room_pair(seed=8, n=700000, m=600000, voxel=0.03, rings=2, iters=30)
+    g = build_grid(dev(P.q), P.voxel, P.rings).dilate(P.rings)
+    p = dev(P.p)
+    autotune_cache_clear()
+    t0 = time.perf_counter()
+    g.autotune(p, searches_per_plan=30)
+    tuning = time.perf_counter() - t0
+    once = []
+    for _ in range(4):
+        t0 = time.perf_counter()
+        g.register(p, 30)
+        once.append(time.perf_counter() - t0)
+    assert tuning < 300 * min(once), (tuning, once)
 
 
 def test_the_launches_are_tuned_where_the_loop_applies():
