@@ -131,7 +131,7 @@ def main():
             g.set_build_schedule(cb, bool(fu), ti, rb)
     schedule = g.schedule
     tf = lambda b: "true" if b else "false"
-    # the variant that runs: registration form over segments, single pair
+    # the launch-per-step form's variant: registration over segments, single pair
     nns_variant = (f"k_nns_local<{schedule['nns_block']}, {schedule['lanes_per_query']}, "
                    f"{tf(schedule['sort_source'])}, true, false, {schedule['search_mode']}, true>")
     # one moment record per search wave
@@ -163,9 +163,10 @@ def main():
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     log("[bench] timed region done")
+    one_launch = g.last_form == _lib.FORM_LOOP   # all iterations of a step in one launch (k_icp_loop)
     ms = (t1 - t0) * 1e3 / a.steps
     # the two parts of a step on their own: the grid refill + dilation, and
-    # the registration (one graph replay of the K iterations)
+    # the registration (one call of K iterations)
     reps = max(5, min(a.steps, 20))
     torch.cuda.synchronize()
     tb = time.perf_counter()
@@ -254,6 +255,8 @@ def main():
                     "limiter": limiter,
                     "flops_per_byte": SEARCH_FLOPS_PER_BYTE, "machine_balance_flops_per_byte": round(balance, 2),
                     "timing": "mean of the per-launch start/stop HIP events of the eager timing pass",
+                    "runs_in": ("the launch-per-step form of the timing pass; the timed step runs its iterations in "
+                                "one launch of k_icp_loop" if one_launch else "the timed step"),
                     "algorithmic_bytes_per_launch": int(bytes_per_launch),
                     "mean_candidates_per_query": round(float(cand.mean()) / P.m, 3),
                     "dilated_lookup_fraction": round(float(dil.mean()) / P.m, 4)}

@@ -101,7 +101,7 @@ typedef struct vicp_icp_opts {
     int32_t early_stop; /* ... only if non-zero; 0 runs exactly K iterations */
     int32_t use_graph;  /* non-zero: capture the K iterations once in a hipGraph and replay it, where they
                             do not run in one launch (sources of up to two units of 16 waves per
-                            compute unit do) */
+                            compute unit do; of one, on grids of 4 points a voxel and more) */
     int32_t global_only; /* non-zero: every query takes the exact global search (ICP with exhaustive
                             NNS, the "Brute" comparator of Table 2); the grid is not consulted */
     int32_t layout;      /* 0: the segmented, offset-addressed layout (Alg. 2-4); 1: VANICP's
